@@ -154,7 +154,7 @@ def prepare(case, seed):
     par = _parents(case, seed)
     t, d = _logits(case, B * N, g)
     t, d = t.view(B, N, V), d.view(B, N, V)
-    parent = torch.as_tensor(np.array(par), dtype=torch.int32, device="cuda")
+    parent = torch.as_tensor(np.array(par, order="C"), dtype=torch.int32, device="cuda")
     if case["call"] == "draft":
         kw.pop("mode")
         return dict(case=case, kw=dict(kw, seed=seed), args=(d, parent))
