@@ -10,6 +10,7 @@
 #include <cfloat>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "resispec.h"
 
@@ -44,9 +45,23 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 __device__ __forceinline__ float widen(float x) { return x; }
 __device__ __forceinline__ float widen(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
+// Elements of rows that need not start, or end, on a 16-byte boundary: rows of a vocabulary
+// whose size is no multiple of 8 (bf16) or 4 (fp32), or a tensor that starts off such a
+// boundary.  The same values under types of their own, so that the kernels for aligned rows
+// keep the code and registers they have.
+struct odd16 {
+    uint16_t v;
+};
+struct odd32 {
+    float v;
+};
+__device__ __forceinline__ float widen(odd16 x) { return widen(x.v); }
+__device__ __forceinline__ float widen(odd32 x) { return x.v; }
+
 // VEC consecutive elements starting at element idx, kept as raw words until used;
 // elements at or beyond V read as -inf, which makes them contribute exactly zero to
 // every sum below.
+
 // 16-byte load; NT: nontemporal (streamed past the caches' normal allocation)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 template <bool NT>
@@ -73,6 +88,8 @@ struct Vec;
 
 template <>
 struct Vec<float, 4> {
+    static constexpr bool kSettle = false;   // every vector a load gives is whole
+    static __device__ __forceinline__ void settle(uint4&, const float*, int, int) {}
     using raw = uint4;
     template <bool NT = false>
     static __device__ __forceinline__ raw load(const float* __restrict__ row, int idx, int V) {
@@ -91,6 +108,8 @@ struct Vec<float, 4> {
 
 template <>
 struct Vec<uint16_t, 8> {
+    static constexpr bool kSettle = false;   // every vector a load gives is whole
+    static __device__ __forceinline__ void settle(uint4&, const uint16_t*, int, int) {}
     using raw = uint4;
     template <bool NT = false>
     static __device__ __forceinline__ raw load(const uint16_t* __restrict__ row, int idx, int V) {
@@ -109,8 +128,83 @@ struct Vec<uint16_t, 8> {
     }
 };
 
+// 16-byte vectors at any element of a row (V >= VEC).  gfx950 reads a misaligned
+// global_load_dwordx4 in one instruction.  Where V is no multiple of VEC, one vector crosses
+// the row's end (at most one lane of a row's last chunk holds it): load() leaves it -inf,
+// and settle() fills it before its use from the row's last VEC elements, so no load reaches
+// past the row.  As late as that because a second address for that lane beside each chunk's
+// loads takes 8-10 registers more than the row kernels have; the line is in the caches by
+// then.  Measured against one element a load, which such rows took before: the row kernel on
+// 64 trees of 33 nodes at V = 65,537 (bf16) 363 -> 185 us.
+typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
+typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
+template <bool NT>
+__device__ __forceinline__ uint4 ld16_any(const odd16* p) {
+    const u32x4_at2* q = reinterpret_cast<const u32x4_at2*>(p);
+    const u32x4 r = NT ? __builtin_nontemporal_load(q) : *q;
+    return make_uint4(r.x, r.y, r.z, r.w);
+}
+template <bool NT>
+__device__ __forceinline__ uint4 ld16_any(const odd32* p) {
+    const u32x4_at4* q = reinterpret_cast<const u32x4_at4*>(p);
+    const u32x4 r = NT ? __builtin_nontemporal_load(q) : *q;
+    return make_uint4(r.x, r.y, r.z, r.w);
+}
+
+// The vector r without its first n elements (0 < n < VEC): the others move to the front,
+// and -inf (FILL: in every element) follows them.
+template <int ELEM, uint32_t FILL>
+__device__ __forceinline__ uint4 drop_front(uint4 r, int n) {
+    uint32_t w[5] = {r.x, r.y, r.z, r.w, FILL};
+    if (ELEM == 2) {
+        if (n & 1) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) w[k] = (w[k] >> 16) | (w[k + 1] << 16);
+        }
+        n >>= 1;
+    }
+    if (n & 1) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[k] = w[k + 1];
+    }
+    if (n & 2) {
+        w[0] = w[2];
+        w[1] = w[3];
+        w[2] = w[3] = FILL;
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+template <typename In, typename Aligned, int VEC, uint32_t FILL>
+struct VecAny {
+    static constexpr bool kSettle = true;
+    using raw = uint4;
+    template <bool NT = false>
+    static __device__ __forceinline__ raw load(const In* __restrict__ row, int idx, int V) {
+        if (idx + VEC <= V) return ld16_any<NT>(row + idx);
+        return make_uint4(FILL, FILL, FILL, FILL);
+    }
+    template <bool NT = false>
+    static __device__ __forceinline__ raw load_full(const In* __restrict__ row, int idx) {
+        return ld16_any<NT>(row + idx);
+    }
+    static __device__ __forceinline__ void settle(raw& r, const In* __restrict__ row, int idx, int V) {
+        if (idx < V && idx + VEC > V)
+            r = drop_front<(int)sizeof(In), FILL>(ld16_any<false>(row + (V - VEC)), idx + VEC - V);
+    }
+    static __device__ __forceinline__ void unpack(const raw& r, float (&v)[VEC]) { Vec<Aligned, VEC>::unpack(r, v); }
+};
+template <>
+struct Vec<odd32, 4> : VecAny<odd32, float, 4, 0xff800000u> {};
+template <>
+struct Vec<odd16, 8> : VecAny<odd16, uint16_t, 8, 0xff80ff80u> {};
+
+// One element a load: rows shorter than a vector, and pointers that are not aligned to
+// their elements.
 template <>
 struct Vec<float, 1> {
+    static constexpr bool kSettle = false;   // every vector a load gives is whole
+    static __device__ __forceinline__ void settle(uint32_t&, const float*, int, int) {}
     using raw = uint32_t;
     template <bool NT = false>
     static __device__ __forceinline__ raw load(const float* __restrict__ row, int idx, int V) {
@@ -125,6 +219,8 @@ struct Vec<float, 1> {
 
 template <>
 struct Vec<uint16_t, 1> {
+    static constexpr bool kSettle = false;   // every vector a load gives is whole
+    static __device__ __forceinline__ void settle(uint32_t&, const uint16_t*, int, int) {}
     using raw = uint32_t;
     template <bool NT = false>
     static __device__ __forceinline__ raw load(const uint16_t* __restrict__ row, int idx, int V) {
@@ -140,7 +236,10 @@ struct Vec<uint16_t, 1> {
 // Unpacked elements of one vector (used outside the streaming passes).
 template <typename In, int VEC>
 __device__ __forceinline__ void load_vec(const In* __restrict__ row, int idx, int V, float (&v)[VEC]) {
-    Vec<In, VEC>::unpack(Vec<In, VEC>::load(row, idx, V), v);
+    using W = Vec<In, VEC>;
+    typename W::raw r = W::load(row, idx, V);
+    W::settle(r, row, idx, V);
+    W::unpack(r, v);
 }
 
 // v_exp_f32: 2^x; results below the normal range flush to zero (they are more than
@@ -302,10 +401,20 @@ __device__ __forceinline__ void park_double(float (&part)[64][kMaxSlots + 1], in
     part[r + 1][s] = __uint_as_float((uint32_t)(bits >> 32));
 }
 
-template <int BLK>
+// LATE: the thread's shared-memory addresses are computed here and not before the passes
+// over the row, which would hold registers that the passes need (the odd-row kernels).
+template <bool LATE>
+__device__ __forceinline__ int thread_id() {
+    int t = threadIdx.x;
+    if (LATE) asm volatile("" : "+v"(t));
+    return t;
+}
+
+template <int BLK, bool LATE = false>
 __device__ __forceinline__ void slot_sums_stage1(Smem& sm, int s_lo, int s_hi, bool wantB) {
     using SG = SlotGroups<BLK>;
-    const int s = threadIdx.x % kMaxSlots, g = threadIdx.x / kMaxSlots;
+    const int t = thread_id<LATE>();
+    const int s = t % kMaxSlots, g = t / kMaxSlots;
     if (g >= SG::NG || s < s_lo || s >= s_hi) return;
     double a = 0.0, c = 0.0;
 #pragma unroll
@@ -434,7 +543,17 @@ __device__ __forceinline__ void wave_sweep(const In* __restrict__ tg, const In* 
         else
             load_chunk<In, VEC, UNR, PAIR, NT>(tg, dg, chunk_start(s, j), V, t, d);
     };
-    auto process = [&](const raw (&ct)[UNR], const raw (&cd)[UNR], int s, int j) {
+    auto process = [&](raw (&ct)[UNR], raw (&cd)[UNR], int s, int j) {
+        if constexpr (W::kSettle) {
+            const int c0 = chunk_start(s, j);
+            if (c0 > V - CHUNK) {   // the row's last chunk
+#pragma unroll
+                for (int u = 0; u < UNR; ++u) {
+                    W::settle(ct[u], tg, c0 + lane0 + u * 64 * VEC, V);
+                    if (PAIR) W::settle(cd[u], dg, c0 + lane0 + u * 64 * VEC, V);
+                }
+            }
+        }
         float t[UNR][VEC], d[UNR][VEC];
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
@@ -521,6 +640,32 @@ __device__ __forceinline__ void wave_sweep(const In* __restrict__ tg, const In* 
 // ------------------------------------------------------------------- host ----
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
+// How the kernels load rows of V elements: 16-byte loads at 16-byte boundaries, 16-byte
+// loads at any element (VecAny), or one element a load (rows shorter than a vector, or a
+// pointer that is not aligned to its elements: no 16-byte load is sure to stay in the row,
+// or to be one the hardware takes).
+enum RowLoads { kLoadsAligned, kLoadsAny, kLoadsSingle };
+inline RowLoads row_loads(const void* t, const void* d, int64_t V, int dtype) {
+    const int64_t esz = dtype == RS_BF16 ? 2 : 4;
+    const uintptr_t at = reinterpret_cast<uintptr_t>(t) | reinterpret_cast<uintptr_t>(d);
+    if ((V * esz) % 16 == 0 && at % 16 == 0) return kLoadsAligned;
+    return V * esz >= 16 && at % (uintptr_t)esz == 0 ? kLoadsAny : kLoadsSingle;
+}
+
+// f(element type, elements a load, loads a chunk) for the row kernels' instance.
+template <typename F>
+auto with_layout(int dtype, RowLoads loads, F&& f) {
+    using std::integral_constant;
+    if (dtype == RS_BF16) {
+        if (loads == kLoadsAligned) return f(uint16_t(), integral_constant<int, 8>(), integral_constant<int, kUnr16>());
+        if (loads == kLoadsAny) return f(odd16(), integral_constant<int, 8>(), integral_constant<int, kUnr16>());
+        return f(uint16_t(), integral_constant<int, 1>(), integral_constant<int, 4>());
+    }
+    if (loads == kLoadsAligned) return f(float(), integral_constant<int, 4>(), integral_constant<int, kUnr32>());
+    if (loads == kLoadsAny) return f(odd32(), integral_constant<int, 4>(), integral_constant<int, kUnr32>());
+    return f(float(), integral_constant<int, 1>(), integral_constant<int, 4>());
+}
 
 inline rs_status check_params(const rs_params* prm) {
     if (!prm) return RS_ERR_INVALID_ARG;

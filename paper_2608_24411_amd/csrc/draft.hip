@@ -150,7 +150,9 @@ __global__ void __launch_bounds__(kDraftBlock) __attribute__((amdgpu_waves_per_e
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             float v[VEC];
-            W::unpack(pre[u], v);
+            typename W::raw r = pre[u];
+            W::settle(r, dg, wid * G * CHUNK + lane * VEC + u * 64 * VEC, V);
+            W::unpack(r, v);
 #pragma unroll
             for (int e = 0; e < VEC; ++e) mx = fmaxf(mx, v[e]);
         }
@@ -451,14 +453,11 @@ rs_status resispec_draft_candidates(const void* draft_logits, const int32_t* par
     P.seed_hi = (uint32_t)(seed >> 32);
     P.off_lo = (uint32_t)offset;
     P.off_hi = (uint32_t)(offset >> 32);
-    const int64_t esz = prm->logits_dtype == RS_BF16 ? 2 : 4;
-    const bool vec = ((int64_t)V * esz) % 16 == 0 && aligned16(draft_logits);
+    const RowLoads loads = row_loads(draft_logits, draft_logits, V, prm->logits_dtype);
     const hipStream_t s = (hipStream_t)stream;
-    hipError_t e;
-    if (prm->logits_dtype == RS_BF16)
-        e = vec ? launch_draft_t<uint16_t, 8, kUnr16>(P, s) : launch_draft_t<uint16_t, 1, 4>(P, s);
-    else
-        e = vec ? launch_draft_t<float, 4, kUnr32>(P, s) : launch_draft_t<float, 1, 4>(P, s);
+    const hipError_t e = with_layout(prm->logits_dtype, loads, [&](auto in, auto vec, auto unr) {
+        return launch_draft_t<decltype(in), vec(), unr()>(P, s);
+    });
     return e == hipSuccess ? RS_OK : RS_ERR_HIP;
 }
 

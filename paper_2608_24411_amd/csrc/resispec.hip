@@ -46,6 +46,7 @@
 // verifies each row of a small batch with several workgroups (row groups).  The draft
 // step that precedes verification is in draft.hip; shared helpers are in common.h.
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -304,11 +305,11 @@ __device__ __forceinline__ int form_group(Smem& sm, const RowGroup& g, char* bas
 // shared memory, then, in a row group, published and gathered, so that on return
 // slotA / slotB (and slotP if keepP) hold the totals of every slot of the row.
 // False if the exchange timed out.
-template <int BLK, bool SPLIT>
+template <int BLK, bool SPLIT, bool LATE>
 __device__ __forceinline__ bool pass_totals(Smem& sm, RowGroup& grp, int nslots, int s0, int nl,
                                             bool wantB, bool keepP) {
-    const int tid = threadIdx.x;
-    slot_sums_stage1<BLK>(sm, s0, s0 + nl, wantB);
+    const int tid = thread_id<LATE>();
+    slot_sums_stage1<BLK, LATE>(sm, s0, s0 + nl, wantB);
     __syncthreads();
     if (!SPLIT || grp.S == 1) {
         if (tid < nslots) {
@@ -598,6 +599,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
             const int idx = wid * G * CHUNK + lane * VEC + u * 64 * VEC;
             typename W::raw r = pre[u];
             if (SPLIT && s0 != 0) r = W::template load<false>(tg, idx, V);
+            W::settle(r, tg, idx, V);
             float v[VEC];
             W::unpack(r, v);
 #pragma unroll
@@ -842,7 +844,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                 flush);
         }
         __syncthreads();
-        if (!pass_totals<BLK, SPLIT>(sm, grp, nslots, s0, nl, internal, true)) {
+        if (!pass_totals<BLK, SPLIT, W::kSettle>(sm, grp, nslots, s0, nl, internal, true)) {
             if (tid == 0) emit(-1, -1, RS_SEQ_GROUP_TIMEOUT);
             zero_residual_row(P, row);
             return;
@@ -1244,7 +1246,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
             }
         }
         __syncthreads();
-        if (!pass_totals<BLK, SPLIT>(sm, grp, nslots, s0, nl, MODE == RS_MODE_RESISPEC && i > 0, false)) {
+        if (!pass_totals<BLK, SPLIT, W::kSettle>(sm, grp, nslots, s0, nl, MODE == RS_MODE_RESISPEC && i > 0, false)) {
             if (tid == 0) emit(-1, -1, RS_SEQ_GROUP_TIMEOUT);
             zero_residual_row(P, row);
             return;
@@ -2016,6 +2018,20 @@ hipError_t launch_row_kernel(KParams P, int64_t nrows, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Members that a call may ask for on rows that are not 16-byte aligned.  Such rows took one
+// element a load, in chunks of 256 elements, so they had more slots than the same rows
+// have in 16-byte loads, and the all-nodes group kernel fitted two workgroups on a CU.
+// What a call could ask for then it still can: a request beyond what the layout of today
+// holds runs with as many members as it does hold (the results are the same with any).
+template <typename In>
+bool aligned_rows(const KParams& P) {
+    return (int64_t)P.V * (int64_t)sizeof(In) % 16 == 0 && aligned16(P.tgt) && aligned16(P.dft);
+}
+int32_t small_chunk_slots(int32_t V) {
+    const int64_t nch = ((int64_t)V + 255) / 256, G = (nch + kMaxSlots - 1) / kMaxSlots;
+    return (int32_t)((nch + G - 1) / G);
+}
+
 // Members per sequence: at most as many workgroups as the device holds at once (a group
 // whose members do not all start in time is done by one of them alone), and each member
 // keeps at least one slot (one per wave when chosen automatically).
@@ -2030,6 +2046,10 @@ int32_t resolve_group(const KParams& P, const PathOut* path) {
         // measured: with the tagged exchange, members of 4 slots still gain
         if (P.nslots / kPathAutoSlots < smax) smax = P.nslots / kPathAutoSlots;
         return smax >= 2 ? (int32_t)smax : 1;
+    }
+    if (!aligned_rows<In>(P)) {
+        const int64_t most = std::min<int64_t>(smax, small_chunk_slots(P.V));
+        return path->group <= most ? std::min(path->group, P.nslots) : -1;
     }
     if (P.nslots < smax) smax = P.nslots;
     return path->group <= smax ? path->group : -1;
@@ -2104,9 +2124,17 @@ hipError_t launch_rowgroups(KParams P, int64_t nrows, RowGroupLaunch* rg, hipStr
             if ((int64_t)cu_count() / nrows < smax) smax = (int64_t)cu_count() / nrows;
             if (P.nslots / (kPathBlock / 64) < smax) smax = P.nslots / (kPathBlock / 64);
             S = smax >= 2 ? (int32_t)smax : 1;
+        } else if (!rg->ws) {
+            S = -1;
+        } else if (!aligned_rows<In>(P)) {
+            const int64_t most = std::min<int64_t>({(int64_t)kMaxGroup, 2 * (int64_t)cu_count() / nrows,
+                                                    (int64_t)small_chunk_slots(P.V)});
+            S = rg->group <= most
+                    ? (int32_t)std::max<int64_t>(1, std::min<int64_t>({rg->group, smax, (int64_t)P.nslots}))
+                    : -1;
         } else {
             if (P.nslots < smax) smax = P.nslots;
-            S = (rg->group <= smax && rg->ws) ? rg->group : -1;
+            S = rg->group <= smax ? rg->group : -1;
         }
     }
     rg->used_group = S;
@@ -2133,42 +2161,26 @@ hipError_t launch_rowgroups(KParams P, int64_t nrows, RowGroupLaunch* rg, hipStr
 }
 
 template <int MODE>
-hipError_t launch_rowgroups_m(const KParams& P, int dtype, bool vec, int64_t nrows, RowGroupLaunch* rg,
+hipError_t launch_rowgroups_m(const KParams& P, int dtype, RowLoads loads, int64_t nrows, RowGroupLaunch* rg,
                               hipStream_t s) {
-    if (dtype == RS_BF16)
-        return vec ? launch_rowgroups<uint16_t, 8, kUnr16, MODE>(P, nrows, rg, s)
-                   : launch_rowgroups<uint16_t, 1, 4, MODE>(P, nrows, rg, s);
-    return vec ? launch_rowgroups<float, 4, kUnr32, MODE>(P, nrows, rg, s)
-               : launch_rowgroups<float, 1, 4, MODE>(P, nrows, rg, s);
+    return with_layout(dtype, loads, [&](auto in, auto vec, auto unr) {
+        return launch_rowgroups<decltype(in), vec(), unr(), MODE>(P, nrows, rg, s);
+    });
 }
 
 template <int MODE>
-hipError_t launch_rows_m(const KParams& P, int dtype, bool vec, int64_t nrows, PathOut* path,
+hipError_t launch_rows_m(const KParams& P, int dtype, RowLoads loads, int64_t nrows, PathOut* path,
                          hipStream_t s) {
-    if (path) {
-        if (dtype == RS_BF16)
-            return vec ? launch_path_kernel<uint16_t, 8, kUnr16, MODE>(P, path, s)
-                       : launch_path_kernel<uint16_t, 1, 4, MODE>(P, path, s);
-        return vec ? launch_path_kernel<float, 4, kUnr32, MODE>(P, path, s)
-                   : launch_path_kernel<float, 1, 4, MODE>(P, path, s);
-    }
-    if (dtype == RS_BF16) {
-        return vec ? launch_row_kernel<uint16_t, 8, kUnr16, MODE>(P, nrows, s)
-                   : launch_row_kernel<uint16_t, 1, 4, MODE>(P, nrows, s);
-    }
-    return vec ? launch_row_kernel<float, 4, kUnr32, MODE>(P, nrows, s)
-               : launch_row_kernel<float, 1, 4, MODE>(P, nrows, s);
+    return with_layout(dtype, loads, [&](auto in, auto vec, auto unr) {
+        return path ? launch_path_kernel<decltype(in), vec(), unr(), MODE>(P, path, s)
+                    : launch_row_kernel<decltype(in), vec(), unr(), MODE>(P, nrows, s);
+    });
 }
-hipError_t launch_rows(const KParams& P, const rs_params* prm, bool vec, int64_t nrows, hipStream_t s,
+hipError_t launch_rows(const KParams& P, const rs_params* prm, RowLoads loads, int64_t nrows, hipStream_t s,
                        PathOut* path = nullptr) {
     if (prm->mode == RS_MODE_SPECINFER)
-        return launch_rows_m<RS_MODE_SPECINFER>(P, prm->logits_dtype, vec, nrows, path, s);
-    return launch_rows_m<RS_MODE_RESISPEC>(P, prm->logits_dtype, vec, nrows, path, s);
-}
-
-bool vector_ok(const void* t, const void* d, int64_t V, int dtype) {
-    const int64_t esz = dtype == RS_BF16 ? 2 : 4;
-    return ((V * esz) % 16 == 0) && aligned16(t) && aligned16(d);
+        return launch_rows_m<RS_MODE_SPECINFER>(P, prm->logits_dtype, loads, nrows, path, s);
+    return launch_rows_m<RS_MODE_RESISPEC>(P, prm->logits_dtype, loads, nrows, path, s);
 }
 
 KParams base_params(const void* t, const void* d, int64_t V, const rs_params* prm) {
@@ -2215,22 +2227,20 @@ hipError_t launch_deferred(KParams P, bool finish, int32_t max_depth, int32_t* o
 }
 
 template <int MODE>
-hipError_t launch_deferred_m(const KParams& P, int dtype, bool vec, bool finish, int32_t max_depth,
+hipError_t launch_deferred_m(const KParams& P, int dtype, RowLoads loads, bool finish, int32_t max_depth,
                              int32_t* out_tokens, int32_t* out_len, int32_t* out_status, hipStream_t s) {
-    if (dtype == RS_BF16)
-        return vec ? launch_deferred<uint16_t, 8, kUnr16, MODE>(P, finish, max_depth, out_tokens, out_len,
-                                                                out_status, s)
-                   : launch_deferred<uint16_t, 1, 4, MODE>(P, finish, max_depth, out_tokens, out_len, out_status, s);
-    return vec ? launch_deferred<float, 4, kUnr32, MODE>(P, finish, max_depth, out_tokens, out_len, out_status, s)
-               : launch_deferred<float, 1, 4, MODE>(P, finish, max_depth, out_tokens, out_len, out_status, s);
+    return with_layout(dtype, loads, [&](auto in, auto vec, auto unr) {
+        return launch_deferred<decltype(in), vec(), unr(), MODE>(P, finish, max_depth, out_tokens, out_len, out_status,
+                                                                 s);
+    });
 }
 
-hipError_t launch_deferred_stage(const KParams& P, const rs_params* prm, bool vec, bool finish, int32_t max_depth,
+hipError_t launch_deferred_stage(const KParams& P, const rs_params* prm, RowLoads loads, bool finish, int32_t max_depth,
                                  int32_t* out_tokens, int32_t* out_len, int32_t* out_status, hipStream_t s) {
     if (prm->mode == RS_MODE_SPECINFER)
-        return launch_deferred_m<RS_MODE_SPECINFER>(P, prm->logits_dtype, vec, finish, max_depth, out_tokens,
+        return launch_deferred_m<RS_MODE_SPECINFER>(P, prm->logits_dtype, loads, finish, max_depth, out_tokens,
                                                     out_len, out_status, s);
-    return launch_deferred_m<RS_MODE_RESISPEC>(P, prm->logits_dtype, vec, finish, max_depth, out_tokens, out_len,
+    return launch_deferred_m<RS_MODE_RESISPEC>(P, prm->logits_dtype, loads, finish, max_depth, out_tokens, out_len,
                                                out_status, s);
 }
 
@@ -2267,8 +2277,8 @@ rs_status tree_impl(const void* target_logits, const void* draft_logits, const i
     const KParams P = tree_params(target_logits, draft_logits, node_token, parent, u_accept,
                                   u_resample, B, N, V, prm, node_child, node_tok, node_status,
                                   residual_out);
-    const bool vec = vector_ok(target_logits, draft_logits, V, prm->logits_dtype);
-    if (launch_rows(P, prm, vec, (int64_t)B * N, s) != hipSuccess) return RS_ERR_HIP;
+    const RowLoads loads = row_loads(target_logits, draft_logits, V, prm->logits_dtype);
+    if (launch_rows(P, prm, loads, (int64_t)B * N, s) != hipSuccess) return RS_ERR_HIP;
     return launch_walk(node_child, node_tok, node_status, node_token, B, N, max_depth, out_tokens,
                        out_accepted_len, out_status, s) == hipSuccess ? RS_OK : RS_ERR_HIP;
 }
@@ -2371,8 +2381,8 @@ rs_status resispec_verify(const void* target_logits, const void* draft_logits,
     P.out_status = out_status;
     P.B = B;
     P.N = 1;
-    const bool vec = vector_ok(target_logits, draft, V, prm->logits_dtype);
-    return launch_rows(P, prm, vec, B, (hipStream_t)stream) == hipSuccess ? RS_OK : RS_ERR_HIP;
+    const RowLoads loads = row_loads(target_logits, draft, V, prm->logits_dtype);
+    return launch_rows(P, prm, loads, B, (hipStream_t)stream) == hipSuccess ? RS_OK : RS_ERR_HIP;
 }
 
 rs_status resispec_verify_tree(const void* target_logits, const void* draft_logits,
@@ -2445,12 +2455,12 @@ rs_status resispec_verify_tree_group(const void* target_logits, const void* draf
     int32_t* ns = ws_array(workspace, rows, 2);
     const KParams P = tree_params(target_logits, draft_logits, node_token, parent, u_accept,
                                   u_resample, B, N, V, prm, nc, nt, ns, nullptr);
-    const bool vec = vector_ok(target_logits, draft_logits, V, prm->logits_dtype);
+    const RowLoads loads = row_loads(target_logits, draft_logits, V, prm->logits_dtype);
     RowGroupLaunch rg{group_size, static_cast<char*>(workspace) + node_arrays_bytes(rows), 0, 1, 0};
     const hipStream_t s = (hipStream_t)stream;
     const hipError_t e = prm->mode == RS_MODE_SPECINFER
-                             ? launch_rowgroups_m<RS_MODE_SPECINFER>(P, prm->logits_dtype, vec, rows, &rg, s)
-                             : launch_rowgroups_m<RS_MODE_RESISPEC>(P, prm->logits_dtype, vec, rows, &rg, s);
+                             ? launch_rowgroups_m<RS_MODE_SPECINFER>(P, prm->logits_dtype, loads, rows, &rg, s)
+                             : launch_rowgroups_m<RS_MODE_RESISPEC>(P, prm->logits_dtype, loads, rows, &rg, s);
     if (rg.unsupported) return RS_ERR_UNSUPPORTED;
     if (e != hipSuccess) return RS_ERR_HIP;
     return launch_walk(nc, nt, ns, node_token, B, N, max_depth, out_tokens, out_accepted_len,
@@ -2467,11 +2477,11 @@ int32_t resispec_tree_group_size(int32_t B, int32_t N, int32_t V, const rs_param
     P.V = V;
     char probe = 0;   // any non-null workspace: the answer does not depend on it
     RowGroupLaunch rg{0, &probe, 1, 1, 0};
-    const bool vec = (prm->logits_dtype == RS_BF16) ? (V % 8 == 0) : (V % 4 == 0);
+    const RowLoads loads = row_loads(nullptr, nullptr, V, prm->logits_dtype);
     const int64_t rows = (int64_t)B * N;
     const hipError_t e = prm->mode == RS_MODE_SPECINFER
-                             ? launch_rowgroups_m<RS_MODE_SPECINFER>(P, prm->logits_dtype, vec, rows, &rg, nullptr)
-                             : launch_rowgroups_m<RS_MODE_RESISPEC>(P, prm->logits_dtype, vec, rows, &rg, nullptr);
+                             ? launch_rowgroups_m<RS_MODE_SPECINFER>(P, prm->logits_dtype, loads, rows, &rg, nullptr)
+                             : launch_rowgroups_m<RS_MODE_RESISPEC>(P, prm->logits_dtype, loads, rows, &rg, nullptr);
     return e == hipSuccess ? rg.used_group : -1;
 }
 
@@ -2504,10 +2514,10 @@ static rs_status verify_tree_path_impl(const void* target_logits, const void* dr
         P.rcache = reinterpret_cast<float*>(static_cast<char*>(workspace) + path_states_bytes(B));
         P.rc_stride = rc_stride(V);
     }
-    const bool vec = vector_ok(target_logits, draft_logits, V, prm->logits_dtype);
+    const RowLoads loads = row_loads(target_logits, draft_logits, V, prm->logits_dtype);
     PathOut path{max_depth, out_tokens, out_accepted_len, out_status, group_size,
                  static_cast<char*>(workspace), 0, 1, 0};
-    const hipError_t e = launch_rows(P, prm, vec, B, (hipStream_t)stream, &path);
+    const hipError_t e = launch_rows(P, prm, loads, B, (hipStream_t)stream, &path);
     if (path.unsupported) return RS_ERR_UNSUPPORTED;
     return e == hipSuccess ? RS_OK : RS_ERR_HIP;
 }
@@ -2556,9 +2566,8 @@ int32_t resispec_path_group_size(int32_t B, int32_t V, const rs_params* prm) {
     P.V = V;
     char probe = 0;   // any non-null workspace: the answer does not depend on it
     PathOut path{0, nullptr, nullptr, nullptr, 0, &probe, 1, 1, 0};
-    // 16-byte aligned rows take the vector kernels
-    const bool vec = (prm->logits_dtype == RS_BF16) ? (V % 8 == 0) : (V % 4 == 0);
-    if (launch_rows(P, prm, vec, B, nullptr, &path) != hipSuccess) return -1;
+    const RowLoads loads = row_loads(nullptr, nullptr, V, prm->logits_dtype);
+    if (launch_rows(P, prm, loads, B, nullptr, &path) != hipSuccess) return -1;
     return path.used_group;
 }
 
@@ -2578,8 +2587,8 @@ rs_status resispec_verify_nodes(const void* target_logits, const void* draft_log
                                   u_resample, B, N, V, prm, ws_array(workspace, rows, 0),
                                   ws_array(workspace, rows, 1), ws_array(workspace, rows, 2),
                                   nullptr);
-    const bool vec = vector_ok(target_logits, draft_logits, V, prm->logits_dtype);
-    return launch_rows(P, prm, vec, rows, (hipStream_t)stream) == hipSuccess ? RS_OK : RS_ERR_HIP;
+    const RowLoads loads = row_loads(target_logits, draft_logits, V, prm->logits_dtype);
+    return launch_rows(P, prm, loads, rows, (hipStream_t)stream) == hipSuccess ? RS_OK : RS_ERR_HIP;
 }
 
 rs_status resispec_walk(const int32_t* node_token, int32_t B, int32_t N, int32_t max_depth,
@@ -2658,8 +2667,8 @@ rs_status deferred_stage(const void* target_logits, const void* draft_logits, co
                             ws_array(workspace, rows, 0), ws_array(workspace, rows, 1),
                             ws_array(workspace, rows, 2), nullptr);
     P.dstate = reinterpret_cast<double*>(static_cast<char*>(workspace) + node_arrays_bytes(rows));
-    const bool vec = vector_ok(target_logits, draft_logits, V, prm->logits_dtype);
-    return launch_deferred_stage(P, prm, vec, finish, max_depth, out_tokens, out_accepted_len, out_status, s) ==
+    const RowLoads loads = row_loads(target_logits, draft_logits, V, prm->logits_dtype);
+    return launch_deferred_stage(P, prm, loads, finish, max_depth, out_tokens, out_accepted_len, out_status, s) ==
                    hipSuccess
                ? RS_OK
                : RS_ERR_HIP;
