@@ -1552,12 +1552,20 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
 }
 
 
+// Block size where every row has a CU to itself (no more rows than CUs): 12 waves, which keep
+// 1.5 times the loads in flight and issue for three waves a SIMD (up to 168 registers).
+// Measured against 512 threads: 8 rows of V = 32,000 fp32 26.5 -> 23.5 us a call, one
+// tree of 21 such rows (V = 32,001) 31.2 -> 28.4 us, 64 rows of V = 128,257 bf16
+// 136.4 -> 130.1 us.  (16 waves: the bf16 RESISPEC kernel spills 18 registers at 128.)
+// More rows than CUs share CUs in pairs, which hide each other's latencies.
+constexpr int kLoneBlock = 768;
+
 // One workgroup per node row; the grid is node-major: the roots of all sequences first,
 // then node 1, ... (nodes with children, whose rows take rejection passes, come early
 // in a topological numbering, so the grid ends on short rows; an order that mixes
 // sequences' rows runs 1.5x longer on a 128-tree batch because late roots form a tail).
-template <typename In, int VEC, int UNR, int MODE>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) rs_row_kernel(const KParams P) {
+template <typename In, int VEC, int UNR, int MODE, int BLK>
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(BLK == kBlock ? 4 : 3))) rs_row_kernel(const KParams P) {
     __shared__ Smem sm;
     int64_t row;
     int32_t b, n;
@@ -1572,7 +1580,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
         row = (int64_t)b * P.N + n;
     }
     RowGroup solo{1, 0, nullptr, nullptr, 0u, kGroupWaitTicks};
-    verify_row<In, VEC, UNR, MODE, kBlock, false>(P, sm, row, b, n, [&](int32_t child, int32_t tok, int32_t st) {
+    verify_row<In, VEC, UNR, MODE, BLK, false>(P, sm, row, b, n, [&](int32_t child, int32_t tok, int32_t st) {
         write_outcome(P, row, child, tok, st);
     }, solo);
 }
@@ -2014,7 +2022,11 @@ void set_slots(KParams& P) {
 template <typename In, int VEC, int UNR, int MODE>
 hipError_t launch_row_kernel(KParams P, int64_t nrows, hipStream_t s) {
     set_slots<VEC, UNR>(P);
-    hipLaunchKernelGGL((rs_row_kernel<In, VEC, UNR, MODE>), dim3((unsigned)nrows), dim3(kBlock), 0, s, P);
+    if (VEC > 1 && nrows <= cu_count())
+        hipLaunchKernelGGL((rs_row_kernel<In, VEC, UNR, MODE, VEC == 1 ? kBlock : kLoneBlock>), dim3((unsigned)nrows),
+                           dim3(kLoneBlock), 0, s, P);
+    else
+        hipLaunchKernelGGL((rs_row_kernel<In, VEC, UNR, MODE, kBlock>), dim3((unsigned)nrows), dim3(kBlock), 0, s, P);
     return hipGetLastError();
 }
 
@@ -2144,8 +2156,7 @@ hipError_t launch_rowgroups(KParams P, int64_t nrows, RowGroupLaunch* rg, hipStr
     }
     if (rg->dry_run) return hipSuccess;
     if (S == 1) {
-        hipLaunchKernelGGL((rs_row_kernel<In, VEC, UNR, MODE>), dim3((unsigned)nrows), dim3(kBlock), 0, s, P);
-        return hipGetLastError();
+        return launch_row_kernel<In, VEC, UNR, MODE>(P, nrows, s);
     }
     hipLaunchKernelGGL(rs_group_reset, dim3((unsigned)nrows), dim3(kResetBlock), 0, s, rg->ws, (int32_t)nrows);
     const hipError_t e = hipGetLastError();
