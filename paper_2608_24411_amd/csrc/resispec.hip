@@ -1872,6 +1872,22 @@ __global__ void __launch_bounds__(kWalkBlock) rs_walk_kernel(const int32_t* __re
     walk_finish(we, W, out, b, out_len, out_status);
 }
 
+// The three outcome arrays of a workspace, copied in one launch (one element a thread: they
+// are a few hundred KB at most, so a launch is what a copy costs; with three copies the
+// outcomes of 32 trees of 60 nodes and their verification took 284.4 us, with this 280.8 us).
+constexpr int kCopyBlock = 256;
+__global__ void __launch_bounds__(kCopyBlock) rs_outcomes_kernel(const int32_t* __restrict__ src, int64_t stride,
+                                                                 int64_t rows, int32_t* __restrict__ child,
+                                                                 int32_t* __restrict__ tok,
+                                                                 int32_t* __restrict__ status) {
+    const int64_t i = (int64_t)blockIdx.x * kCopyBlock + threadIdx.x;
+    if (i >= rows) return;
+    const int32_t c = src[i], t = src[stride + i], s = src[2 * stride + i];
+    child[i] = c;
+    tok[i] = t;
+    status[i] = s;
+}
+
 // The all-nodes schedule with deferred draws, first launch: every node row's tests, with
 // the draws of single-candidate rejections and leaves deferred (same grid as the row
 // kernel).
@@ -2629,12 +2645,11 @@ rs_status resispec_node_outcomes(const void* workspace, size_t workspace_bytes, 
         return RS_ERR_WORKSPACE;
     const int64_t rows = (int64_t)B * N;
     void* ws = const_cast<void*>(workspace);
-    int32_t* dst[3] = {node_child, node_token_out, node_status};
-    for (int k = 0; k < 3; ++k)
-        if (hipMemcpyAsync(dst[k], ws_array(ws, rows, k), (size_t)rows * sizeof(int32_t),
-                           hipMemcpyDeviceToDevice, (hipStream_t)stream) != hipSuccess)
-            return RS_ERR_HIP;
-    return RS_OK;
+    const int64_t blocks = (rows + kCopyBlock - 1) / kCopyBlock;
+    hipLaunchKernelGGL(rs_outcomes_kernel, dim3((unsigned)blocks), dim3(kCopyBlock), 0, (hipStream_t)stream,
+                       ws_array(ws, rows, 0), ws_array(ws, rows, 1) - ws_array(ws, rows, 0), rows, node_child,
+                       node_token_out, node_status);
+    return hipGetLastError() == hipSuccess ? RS_OK : RS_ERR_HIP;
 }
 
 rs_status resispec_verify_tree_debug(const void* target_logits, const void* draft_logits,
