@@ -270,6 +270,7 @@ __device__ __forceinline__ double dpp_d(double v) {
     const int hi = dpp_i<CTRL>(__double2hiint(v));
     return __hiloint2double(hi, lo);
 }
+constexpr int kDppQuad0 = 0x00, kDppQuad1 = 0x55, kDppQuad2 = 0xAA, kDppQuad3 = 0xFF;
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
 
 __device__ __forceinline__ float readlane_f(float v, int l) {
@@ -382,23 +383,16 @@ struct Smem {
 };
 
 // Per-slot sums of the lane partials of a pass, in a fixed order, so the totals are
-// bitwise reproducible whatever wave processed which slot, and whatever the block size.
-// Stage 1 (the first NG * kMaxSlots threads, for the slots in [s_lo, s_hi)): thread t
-// adds lanes [g*GS, g*GS + GS) of slot t % kMaxSlots, g = t / kMaxSlots, in fp64 and
-// parks the sum in rows g*GS and g*GS + 1 of that column as two 32-bit halves (no other
-// thread touches those cells).  Stage 2, after a barrier (slot_group_sum): the NG group
-// sums of one slot are added in group order.
-template <int BLK>
-struct SlotGroups {
-    static constexpr int NG = 4;
-    static constexpr int GS = 64 / NG;
-    static_assert(NG * kMaxSlots <= BLK, "the block must hold a thread per group and slot");
-};
-
-__device__ __forceinline__ void park_double(float (&part)[64][kMaxSlots + 1], int r, int s, double v) {
-    const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
-    part[r][s] = __uint_as_float((uint32_t)bits);
-    part[r + 1][s] = __uint_as_float((uint32_t)(bits >> 32));
+// bitwise reproducible whatever wave processed which slot, and whatever the block size:
+// thread 4 s + g adds lanes [16 g, 16 g + 16) of slot s in fp64, and the four lanes of a
+// slot then add their sums in the order of g.  (A wave reads 16 slots times 4 groups of
+// rows 16 apart, which fall on 64 different banks.)  Every lane of the four returns the sum.
+constexpr int kSumThreads = 4 * kMaxSlots;
+__device__ __forceinline__ double slot_sum(const float (&part)[64][kMaxSlots + 1], int s, int g) {
+    double a = 0.0;
+#pragma unroll
+    for (int l = 0; l < 16; ++l) a += (double)part[g * 16 + l][s];
+    return ((dpp_d<kDppQuad0>(a) + dpp_d<kDppQuad1>(a)) + dpp_d<kDppQuad2>(a)) + dpp_d<kDppQuad3>(a);
 }
 
 // LATE: the thread's shared-memory addresses are computed here and not before the passes
@@ -408,48 +402,6 @@ __device__ __forceinline__ int thread_id() {
     int t = threadIdx.x;
     if (LATE) asm volatile("" : "+v"(t));
     return t;
-}
-
-template <int BLK, bool LATE = false>
-__device__ __forceinline__ void slot_sums_stage1(Smem& sm, int s_lo, int s_hi, bool wantB) {
-    using SG = SlotGroups<BLK>;
-    const int t = thread_id<LATE>();
-    const int s = t % kMaxSlots, g = t / kMaxSlots;
-    if (g >= SG::NG || s < s_lo || s >= s_hi) return;
-    double a = 0.0, c = 0.0;
-#pragma unroll
-    for (int l = 0; l < SG::GS; ++l) a += (double)sm.partA[g * SG::GS + l][s];
-    if (wantB) {
-#pragma unroll
-        for (int l = 0; l < SG::GS; ++l) c += (double)sm.partB[g * SG::GS + l][s];
-    }
-    park_double(sm.partA, g * SG::GS, s, a);
-    if (wantB) park_double(sm.partB, g * SG::GS, s, c);
-}
-
-// Stage 1 over one array of partials only (kernels with a single sum per slot).
-template <int BLK>
-__device__ __forceinline__ void slot_sums_stage1_one(float (&part)[64][kMaxSlots + 1], int s_lo, int s_hi) {
-    using SG = SlotGroups<BLK>;
-    const int s = threadIdx.x % kMaxSlots, g = threadIdx.x / kMaxSlots;
-    if (g >= SG::NG || s < s_lo || s >= s_hi) return;
-    double a = 0.0;
-#pragma unroll
-    for (int l = 0; l < SG::GS; ++l) a += (double)part[g * SG::GS + l][s];
-    park_double(part, g * SG::GS, s, a);
-}
-
-template <int BLK>
-__device__ __forceinline__ double slot_group_sum(const float (&part)[64][kMaxSlots + 1], int s) {
-    using SG = SlotGroups<BLK>;
-    double v = 0.0;
-#pragma unroll
-    for (int g = 0; g < SG::NG; ++g) {
-        const uint32_t lo = __float_as_uint(part[g * SG::GS][s]);
-        const uint32_t hi = __float_as_uint(part[g * SG::GS + 1][s]);
-        v += __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-    }
-    return v;
 }
 
 // Exponent reference for a maximum m: an integer-valued float near -m * c2, so that

@@ -138,41 +138,6 @@ __device__ __forceinline__ void chain_terms(float R, float Q, int j, const Smem&
     Bv = x0 ? 0.0f : R;
 }
 
-// Scalar chain for the accept test of candidate i (fp64, normalised units): R(x) and
-// D(x) of the candidate.  Returned by value (a call, if the compiler keeps one, passes
-// them in registers rather than through a stack slot).
-struct ResDraft {
-    double R, D;
-};
-template <int MODE>
-__device__ ResDraft scalar_residual(const Smem& sm, int i, double p, double q, int32_t x, bool worep) {
-    bool removed = false;
-    if (worep)
-        for (int t = 0; t < i; ++t) removed |= x == sm.st_x[t];
-    const double Dout = removed ? 0.0 : q * sm.st_ds[i];
-    if (MODE == RS_MODE_SPECINFER) {
-        // the standard recurrence max(R - D, 0) / S applied i times equals
-        // max(p - C q, 0) / Tot (every factor is positive)
-        if (i == 0) return {p, Dout};
-        const double w = p - sm.st_C[i - 1] * q;
-        return {w > 0.0 ? w / sm.st_tot[i - 1] : 0.0, Dout};
-    }
-    double R = p;
-    removed = false;
-    for (int t = 0; t < i; ++t) {
-        const double Dt = removed ? 0.0 : q * sm.st_ds[t];
-        if (x == sm.st_x[t]) {
-            R = 0.0;
-        } else {
-            const double zd = sm.st_zd[t] * Dt;
-            const double m = zd < R ? zd : R;
-            R = ((1.0 - sm.st_ad[t]) * m + sm.st_ad[t] * R) / sm.st_zd[t];
-        }
-        if (worep && x == sm.st_x[t]) removed = true;
-    }
-    return {R, Dout};
-}
-
 // ------------------------------------------------------------ row kernel ----
 
 // Verification of one node row by the whole workgroup: node n of sequence b (row
@@ -254,13 +219,6 @@ __device__ __forceinline__ double join_halves(uint32_t lo, uint32_t hi) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-__device__ __forceinline__ void put_tagged_d(unsigned long long* w, uint32_t tag, double v) {
-    const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
-    put_tagged(w, tag, (uint32_t)bits);
-    put_tagged(w + 1, tag, (uint32_t)(bits >> 32));
-}
-
-
 // Group formation, before a group's first row.  Members are launched as ordinary
 // workgroups, so they need not all be resident at once: each counts its arrival, and
 // the last to arrive marks the group formed.  A member that sees no such mark within
@@ -301,22 +259,26 @@ __device__ __forceinline__ int form_group(Smem& sm, const RowGroup& g, char* bas
     return res;
 }
 
-// Slot totals of the pass just swept (this workgroup's slots [s0, s0 + nl)): summed in
-// shared memory, then, in a row group, published and gathered, so that on return
+// Slot totals of the pass just swept (this workgroup's slots [s0, s0 + nl)): summed by the
+// first kSumThreads threads, then, in a row group, published and gathered, so that on return
 // slotA / slotB (and slotP if keepP) hold the totals of every slot of the row.
 // False if the exchange timed out.
 template <int BLK, bool SPLIT, bool LATE>
 __device__ __forceinline__ bool pass_totals(Smem& sm, RowGroup& grp, int nslots, int s0, int nl,
                                             bool wantB, bool keepP) {
+    static_assert(kSumThreads <= BLK, "the block must hold four threads per slot");
     const int tid = thread_id<LATE>();
-    slot_sums_stage1<BLK, LATE>(sm, s0, s0 + nl, wantB);
-    __syncthreads();
+    const int s = tid >> 2, g = tid & 3;
+    const bool mine = s >= s0 && s < s0 + nl;   // (the same for the four lanes of a slot)
     if (!SPLIT || grp.S == 1) {
-        if (tid < nslots) {
-            const double a = slot_group_sum<BLK>(sm.partA, tid);
-            sm.slotA[tid] = a;
-            sm.slotB[tid] = wantB ? slot_group_sum<BLK>(sm.partB, tid) : 0.0;
-            if (keepP) sm.slotP[tid] = a;
+        if (mine) {
+            const double a = slot_sum(sm.partA, s, g);
+            const double c = wantB ? slot_sum(sm.partB, s, g) : 0.0;
+            if (g == 0) {
+                sm.slotA[s] = a;
+                sm.slotB[s] = c;
+                if (keepP) sm.slotP[s] = a;
+            }
         }
         __syncthreads();
         return true;
@@ -324,10 +286,12 @@ __device__ __forceinline__ bool pass_totals(Smem& sm, RowGroup& grp, int nslots,
     const uint32_t tag = ++grp.epoch;
     unsigned long long* xa = grp.xw + (size_t)(tag & 1u) * (2 * kMaxSlots * 2);
     unsigned long long* xb = xa + kMaxSlots * 2;
-    if (tid < nl) {
-        const int s = s0 + tid;
-        put_tagged_d(xa + 2 * s, tag, slot_group_sum<BLK>(sm.partA, s));
-        if (wantB) put_tagged_d(xb + 2 * s, tag, slot_group_sum<BLK>(sm.partB, s));
+    if (mine) {
+        // lane g of the slot publishes word g: the two halves of A, then those of B
+        const double a = slot_sum(sm.partA, s, g);
+        const double c = wantB ? slot_sum(sm.partB, s, g) : 0.0;
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(g < 2 ? a : c);
+        if (g < 2 || wantB) put_tagged((g < 2 ? xa : xb) + 2 * s + (g & 1), tag, (uint32_t)(g & 1 ? bits >> 32 : bits));
     }
     // every slot's totals, once the member that swept it has published them (the words
     // of a slot are polled together)
@@ -782,6 +746,58 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
         if (kSlotWords > 2) cm2 = __builtin_amdgcn_readfirstlane(sm.cand_slots[kSlotWords > 2 ? 2 : 0]);
         if (kSlotWords > 3) cm3 = __builtin_amdgcn_readfirstlane(sm.cand_slots[kSlotWords > 3 ? 3 : 0]);
     }
+    // The accept test of candidate i (one thread, fp64): R and D are the residual's and the
+    // draft's mass at its token (normalised), s_t and s_d the rows' sums, prev_tot the
+    // standard residual's total after the rejection before it.  Its decision, and
+    // after a rejection the constants of the rejection pass, go to shared memory.
+    auto test = [&](int i, double R, double D, double s_t, double s_d, double prev_tot) __attribute__((always_inline)) {
+        const int32_t x = sm.cand_tok[i];
+        const float u = sm.cand_u[i];
+        int dec = -1;
+        if (x < 0 || x >= V) {
+            sm.status = RS_SEQ_BAD_TOKEN;
+            dec = -2;
+        } else if (!(u >= 0.0f && u < 1.0f)) {
+            sm.status = RS_SEQ_BAD_UNIFORM;
+            dec = -2;
+        } else if (!(D > 0.0)) {
+            sm.status = RS_SEQ_ZERO_DRAFT;
+            dec = -2;
+        } else if ((double)u < R / D) {
+            dec = i;
+        } else {
+            const double z = D - R;   // ResiSpec budget
+            const double q2t = s_t / s_d;
+            sm.st_x[i] = x;
+            sm.st_rx[i] = R;
+            const int hs = (x / CHUNK) / G;
+            sm.hit_slots[hs >> 5] |= 1u << (hs & 31);
+            sm.st_zd[i] = z;
+            if (MODE == RS_MODE_SPECINFER) {
+                const double C = (i == 0) ? sm.st_ds[0]
+                                          : sm.st_C[i - 1] + prev_tot * sm.st_ds[i];
+                sm.st_C[i] = C;
+                sm.st_c[i] = (float)(C * q2t);
+            } else {
+                const double c = z * sm.st_ds[i] * q2t;
+                sm.st_c[i] = (float)c;
+                if (i == 0) {
+                    // c = m 2^e exactly, m in [0.5, 1); log2 m in fp32.  The split
+                    // only has to reproduce c to fp32 accuracy, like st_c itself.
+                    int e;
+                    const double m = frexp(c, &e);
+                    const float f0 = __builtin_amdgcn_logf((float)m);
+                    sm.st_f0 = f0;
+                    sm.st_kq0 = Kd + (float)e;
+                    sm.st_2f0 = (double)exp2_fast(f0);
+                    sm.rx0e = (double)exp2_fast(expo(sm.cand_lt[0], c2h, c2l, Kt));
+                    sm.sx0 = hs;
+                }
+            }
+            sm.next_slot = kWaves;
+        }
+        sm.decision = dec;
+    };
     for (int attempt = 0;; ++attempt) {
         float fa = 0.0f, fc = 0.0f;   // this slot's lane partials
         auto flush = [&](int slot) {
@@ -889,6 +905,22 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                 sm.decision = ok ? -1 : -3;   // -3: sum again with exact maxima
                 sm.next_slot = kWaves;
             }
+            // the candidates' probabilities (fp64, the same exponent constants), one lane
+            // each, and the first test
+            if (ok && lane < nc) {
+                const int32_t x = sm.cand_tok[lane];
+                double pc = 0.0, qc = 0.0;
+                if (x >= 0 && x < V) {
+                    const bool early = holders && !refixed;
+                    const double pe = early ? sm.cand_p[lane] : exp2((double)sm.cand_lt[lane] * c2d + (double)Kt);
+                    const double qe = early ? sm.cand_q[lane] : exp2((double)sm.cand_ld[lane] * c2d + (double)Kd);
+                    pc = pe / s0;
+                    qc = qe / sd;
+                }
+                sm.cand_p[lane] = pc;
+                sm.cand_q[lane] = qc;
+                if (lane == 0) test(0, pc, qc * sm.st_ds[0], s0, sd, 0.0);
+            }
         }
         __syncthreads();
         if (sm.decision != -3) break;
@@ -973,80 +1005,12 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
     const double St = sm.St, Sd = sm.Sd;
     // draft mass in target units: q St / Sd, folded into the step constants
     const double q2t = internal ? St / Sd : 0.0;
-
-    // ---- candidate probabilities in fp64, with the same exponent constants
-    if (tid < nc) {
-        const int32_t x = sm.cand_tok[tid];
-        double pc = 0.0, qc = 0.0;
-        if (x >= 0 && x < V) {
-            const bool early = holders && !refixed;
-            const double pe = early ? sm.cand_p[tid] : exp2((double)sm.cand_lt[tid] * c2d + (double)Kt);
-            const double qe = early ? sm.cand_q[tid] : exp2((double)sm.cand_ld[tid] * c2d + (double)Kd);
-            pc = pe / St;
-            qc = qe / Sd;
-        }
-        sm.cand_p[tid] = pc;
-        sm.cand_q[tid] = qc;
-    }
-    __syncthreads();
-
     const bool worep = P.worep != 0;
 
-    // ---- sequential accept / reject
+    // ---- sequential accept / reject: test i has been taken (by wave 0, with the sums
+    // before it)
     int i = 0;
     for (; i < nc; ++i) {
-        if (tid == 0) {
-            const int32_t x = sm.cand_tok[i];
-            const float u = sm.cand_u[i];
-            int dec = -1;
-            if (x < 0 || x >= V) {
-                sm.status = RS_SEQ_BAD_TOKEN;
-                dec = -2;
-            } else if (!(u >= 0.0f && u < 1.0f)) {
-                sm.status = RS_SEQ_BAD_UNIFORM;
-                dec = -2;
-            } else {
-                const ResDraft rd = scalar_residual<MODE>(sm, i, sm.cand_p[i], sm.cand_q[i], x, worep);
-                const double Rx = rd.R, Dx = rd.D;
-                if (!(Dx > 0.0)) {
-                    sm.status = RS_SEQ_ZERO_DRAFT;
-                    dec = -2;
-                } else if ((double)u < Rx / Dx) {
-                    dec = i;
-                } else {
-                    const double z = Dx - Rx;   // ResiSpec budget
-                    sm.st_x[i] = x;
-                    sm.st_rx[i] = Rx;
-                    const int hs = (x / CHUNK) / G;
-                    sm.hit_slots[hs >> 5] |= 1u << (hs & 31);
-                    sm.st_zd[i] = z;
-                    if (MODE == RS_MODE_SPECINFER) {
-                        const double C = (i == 0) ? sm.st_ds[0]
-                                                  : sm.st_C[i - 1] + sm.st_tot[i - 1] * sm.st_ds[i];
-                        sm.st_C[i] = C;
-                        sm.st_c[i] = (float)(C * q2t);
-                    } else {
-                        const double c = z * sm.st_ds[i] * q2t;
-                        sm.st_c[i] = (float)c;
-                        if (i == 0) {
-                            // c = m 2^e exactly, m in [0.5, 1); log2 m in fp32.  The split
-                            // only has to reproduce c to fp32 accuracy, like st_c itself.
-                            int e;
-                            const double m = frexp(c, &e);
-                            const float f0 = __builtin_amdgcn_logf((float)m);
-                            sm.st_f0 = f0;
-                            sm.st_kq0 = Kd + (float)e;
-                            sm.st_2f0 = (double)exp2_fast(f0);
-                            sm.rx0e = (double)exp2_fast(expo(sm.cand_lt[0], c2h, c2l, Kt));
-                            sm.sx0 = hs;
-                        }
-                    }
-                    sm.next_slot = kWaves;
-                }
-            }
-            sm.decision = dec;
-        }
-        __syncthreads();
         if (sm.decision != -1) break;
         // one candidate, rejected: the draw from the residual is used only if a walk ends here
         if constexpr (SCHED == kSchedDecide) {
@@ -1252,6 +1216,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
             return;
         }
         if (wid == 0) {
+            const int lane = thread_id<true>() & 63;
             // per-lane sums over slots lane, lane+64, ... in a fixed order
             double A = 0.0, Bv = 0.0;
             for (int s2 = lane; s2 < nslots; s2 += 64) {
@@ -1259,8 +1224,10 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                 Bv += sm.slotB[s2];
             }
             const double z = sm.st_zd[i];
+            double next_a;   // ResiSpec: a.  Standard: the residual's total
             if (MODE == RS_MODE_SPECINFER) {
                 const double tot = wave_sum(A) / St;   // normalised units
+                next_a = tot;
                 if (lane == 0) {
                     if (!(tot > 0.0)) {
                         sm.status = RS_SEQ_UNDERFLOW;
@@ -1295,10 +1262,31 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                     sm.st_k1[i] = (float)(a / z);
                     sm.st_kc[i] = (float)((1.0 - a) * sm.st_ds[i] * q2t);   // (1 - a) c / Z
                 }
+                next_a = a;
+            }
+            // the candidates not yet tested, one lane each: the residual at their token after
+            // this rejection, and the draft without the rejected token; then the next test
+            if (lane > i && lane < nc) {
+                const int32_t x = sm.cand_tok[lane];
+                const bool at = x == sm.st_x[i];
+                double Rc = sm.cand_p[lane], q = sm.cand_q[lane];
+                if (MODE == RS_MODE_RESISPEC) {
+                    const double zd = z * (q * sm.st_ds[i]);
+                    const double m = zd < Rc ? zd : Rc;
+                    Rc = at ? 0.0 : ((1.0 - next_a) * m + next_a * Rc) / z;
+                    sm.cand_p[lane] = Rc;
+                } else if (lane == i + 1) {
+                    // the standard recurrence max(R - D, 0) / S applied i + 1 times equals
+                    // max(p - C q, 0) / Tot (every factor is positive)
+                    const double w = Rc - sm.st_C[i] * q;
+                    Rc = w > 0.0 ? w / next_a : 0.0;
+                }
+                if (worep && at) sm.cand_q[lane] = q = 0.0;
+                if (lane == i + 1 && (MODE == RS_MODE_RESISPEC || next_a > 0.0))
+                    test(i + 1, Rc, q * sm.st_ds[i + 1], St, Sd, next_a);
             }
         }
         __syncthreads();
-        if (sm.decision == -2) break;
     }
 
     if (sm.decision == -2) {
