@@ -663,6 +663,10 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
         nc = sm.nc;
         status = sm.status;
     }
+    // A resumed row has one candidate, or none: rows with more draw in the first launch.
+    constexpr bool kOne = SCHED == kSchedResume;
+    constexpr bool kLate = W::kSettle || (kOne && BLK == 512);
+    if (kOne && nc > 1) status = RS_SEQ_BAD_TREE;   // (another tree than the first launch saw)
     if (status != RS_SEQ_OK) {
         if (tid == 0) emit(-1, -1, status);
         zero_residual_row(P, row);
@@ -860,13 +864,14 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                 flush);
         }
         __syncthreads();
-        if (!pass_totals<BLK, SPLIT, W::kSettle>(sm, grp, nslots, s0, nl, internal, true)) {
+        if (!pass_totals<BLK, SPLIT, kLate>(sm, grp, nslots, s0, nl, internal, true)) {
             if (tid == 0) emit(-1, -1, RS_SEQ_GROUP_TIMEOUT);
             zero_residual_row(P, row);
             return;
         }
         }
         if (wid == 0) {
+            const int lane = thread_id<kLate>() & 63;
             double a0 = 0.0, a1 = 0.0;
             for (int s2 = lane; s2 < nslots; s2 += 64) {
                 a0 += sm.slotA[s2];
@@ -1010,8 +1015,9 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
     // ---- sequential accept / reject: test i has been taken (by wave 0, with the sums
     // before it)
     int i = 0;
-    for (; i < nc; ++i) {
+    for (; i < (kOne ? min(nc, 1) : nc); ++i) {
         if (sm.decision != -1) break;
+        const int ii = kOne ? 0 : i;
         // one candidate, rejected: the draw from the residual is used only if a walk ends here
         if constexpr (SCHED == kSchedDecide) {
             if (deferrable && nc == 1) {
@@ -1024,10 +1030,9 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
         // rejection pass: sums of step i with per-slot partials
         {
             float accA = 0.0f, accB = 0.0f;   // this slot's lane partials
-            const bool reverse = (i & 1) == 0;   // re-read the most recently fetched end first
-            const int ii = i;
-            const float ci = sm.st_c[i];
-            const int xi = sm.st_x[i];
+            const bool reverse = (ii & 1) == 0;   // re-read the most recently fetched end first
+            const float ci = sm.st_c[ii];
+            const int xi = sm.st_x[ii];
             // ResiSpec needs the per-slot sums of R only after the first rejection
             const bool wantB = MODE == RS_MODE_RESISPEC && ii > 0;
             auto flush = [&](int slot) {
@@ -1210,7 +1215,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
             }
         }
         __syncthreads();
-        if (!pass_totals<BLK, SPLIT, W::kSettle>(sm, grp, nslots, s0, nl, MODE == RS_MODE_RESISPEC && i > 0, false)) {
+        if (!pass_totals<BLK, SPLIT, kLate>(sm, grp, nslots, s0, nl, MODE == RS_MODE_RESISPEC && ii > 0, false)) {
             if (tid == 0) emit(-1, -1, RS_SEQ_GROUP_TIMEOUT);
             zero_residual_row(P, row);
             return;
@@ -1223,7 +1228,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                 A += sm.slotA[s2];
                 Bv += sm.slotB[s2];
             }
-            const double z = sm.st_zd[i];
+            const double z = sm.st_zd[ii];
             double next_a;   // ResiSpec: a.  Standard: the residual's total
             if (MODE == RS_MODE_SPECINFER) {
                 const double tot = wave_sum(A) / St;   // normalised units
@@ -1233,15 +1238,15 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                         sm.status = RS_SEQ_UNDERFLOW;
                         sm.decision = -2;
                     }
-                    sm.st_tot[i] = tot;
+                    sm.st_tot[ii] = tot;
                 }
                 for (int s2 = lane; s2 < nslots; s2 += 64) sm.slotT[s2] = sm.slotA[s2];
             } else {
                 // GetProxy: M = sum min(Z D, R), SR = sum R (both over j != x_i),
                 // a = (Z - M) / (SR - M)
-                const double scale = (i == 0) ? sm.st_2f0 : 1.0;
+                const double scale = (ii == 0) ? sm.st_2f0 : 1.0;
                 const double M = wave_sum(A) * scale / St;
-                const double SR = (i == 0) ? 1.0 - sm.st_rx[0] : wave_sum(Bv) / St;
+                const double SR = (ii == 0) ? 1.0 - sm.st_rx[0] : wave_sum(Bv) / St;
                 const double C = SR - M;                 // remaining capacity, x0 excluded
                 const double a = (C > 0.0) ? (z - M) / C : 0.0;
                 // slot totals of the unnormalised next residual (linear in the partials);
@@ -1249,29 +1254,29 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                 // without x_0
                 for (int s2 = lane; s2 < nslots; s2 += 64) {
                     double Bs = sm.slotB[s2];
-                    if (i == 0) {
+                    if (ii == 0) {
                         Bs = sm.slotP[s2] - (s2 == sm.sx0 ? sm.rx0e : 0.0);
                         Bs = Bs > 0.0 ? Bs : 0.0;
                     }
                     sm.slotT[s2] = (1.0 - a) * sm.slotA[s2] * scale + a * Bs;
                 }
                 if (lane == 0) {
-                    sm.st_ad[i] = a;
-                    sm.st_a[i] = (float)a;
-                    sm.st_i[i] = (float)(1.0 / z);
-                    sm.st_k1[i] = (float)(a / z);
-                    sm.st_kc[i] = (float)((1.0 - a) * sm.st_ds[i] * q2t);   // (1 - a) c / Z
+                    sm.st_ad[ii] = a;
+                    sm.st_a[ii] = (float)a;
+                    sm.st_i[ii] = (float)(1.0 / z);
+                    sm.st_k1[ii] = (float)(a / z);
+                    sm.st_kc[ii] = (float)((1.0 - a) * sm.st_ds[ii] * q2t);   // (1 - a) c / Z
                 }
                 next_a = a;
             }
             // the candidates not yet tested, one lane each: the residual at their token after
             // this rejection, and the draft without the rejected token; then the next test
-            if (lane > i && lane < nc) {
+            if (!kOne && lane > i && lane < nc) {
                 const int32_t x = sm.cand_tok[lane];
-                const bool at = x == sm.st_x[i];
+                const bool at = x == sm.st_x[ii];
                 double Rc = sm.cand_p[lane], q = sm.cand_q[lane];
                 if (MODE == RS_MODE_RESISPEC) {
-                    const double zd = z * (q * sm.st_ds[i]);
+                    const double zd = z * (q * sm.st_ds[ii]);
                     const double m = zd < Rc ? zd : Rc;
                     Rc = at ? 0.0 : ((1.0 - next_a) * m + next_a * Rc) / z;
                     sm.cand_p[lane] = Rc;
@@ -1310,7 +1315,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
         zero_residual_row(P, row);
         return;
     }
-    const int last = nc - 1;   // index of the last rejection step (internal rows)
+    const int last = kOne ? 0 : nc - 1;   // index of the last rejection step (internal rows)
     const float a_last = (internal && MODE == RS_MODE_RESISPEC) ? sm.st_a[last] : 0.0f;
     const bool first_only = internal && MODE == RS_MODE_RESISPEC && last == 0;
     const float f0 = first_only ? sm.st_f0 : 0.0f, kq0 = first_only ? sm.st_kq0 : 0.0f;
@@ -1373,6 +1378,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
         }
     };
     if (wid == 0) {
+        const int lane = thread_id<kLate>() & 63;
         // slot totals in vocabulary order; lane l holds slots 4l .. 4l+3
         double Ts[4];
         double own = 0.0;
@@ -1896,17 +1902,19 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
 // ends at a row whose draw was deferred, the workgroup takes that row up again (its slot
 // totals from the first launch, then its rejection pass and its draw, or the bonus draw
 // of a leaf: pass 1, then the draw), records the node's outcome and finishes the walk
-// with it.  Its workgroups are few (one per sequence), each streaming a row alone, so
-// they take 12 waves (1.5 times the row kernel's loads in flight) and up to 168
-// registers per lane: the row's code for a leaf, a single-candidate rejection and a row
-// of several candidates is all in this kernel.
+// with it.  Up to one sequence per CU, each workgroup streams a row alone: it takes 12
+// waves (1.5 times the row kernel's loads in flight) and up to 168 registers per lane.
+// More sequences than CUs share CUs in pairs of 512 threads, which hide each other's
+// latencies (walk, description, draw): 1024 serving trees' step 763 -> 737 us.  Such rows
+// have one candidate or none, so the code of later rejections is left out, which is what
+// fits the pairs' 128 registers (the 128 trees of the benchmarked step also gained, 333 ->
+// 329 us).
 constexpr int kFinishBlock = 768;
 
-template <typename In, int VEC, int UNR, int MODE>
-__global__ void __launch_bounds__(kFinishBlock) __attribute__((amdgpu_waves_per_eu(2)))
+template <typename In, int VEC, int UNR, int MODE, int BLK>
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(BLK == kBlock ? 4 : 2)))
 rs_finish_kernel(const KParams P, int32_t max_depth, int32_t* __restrict__ out_tokens,
                  int32_t* __restrict__ out_len, int32_t* __restrict__ out_status) {
-    constexpr int kBlock = kFinishBlock;
     __shared__ Smem sm;
     __shared__ int32_t s_node;
     const int32_t b = blockIdx.x;
@@ -1927,7 +1935,7 @@ rs_finish_kernel(const KParams P, int32_t max_depth, int32_t* __restrict__ out_t
     }
     const int64_t row = base + n;
     RowGroup solo{1, 0, nullptr, nullptr, 0u, kGroupWaitTicks};
-    verify_row<In, VEC, UNR, MODE, kBlock, false, false, kSchedResume>(
+    verify_row<In, VEC, UNR, MODE, BLK, false, false, kSchedResume>(
         P, sm, row, b, n,
         [&](int32_t child, int32_t tok, int32_t st) {
             write_outcome(P, row, child, tok, st);
@@ -2232,9 +2240,14 @@ template <typename In, int VEC, int UNR, int MODE>
 hipError_t launch_deferred(KParams P, bool finish, int32_t max_depth, int32_t* out_tokens, int32_t* out_len,
                            int32_t* out_status, hipStream_t s) {
     set_slots<VEC, UNR>(P);
-    if (finish)
-        hipLaunchKernelGGL((rs_finish_kernel<In, VEC, UNR, MODE>), dim3((unsigned)P.B), dim3(kFinishBlock), 0, s, P,
-                           max_depth, out_tokens, out_len, out_status);
+    // (the odd fp32 rows' kernel does not fit two workgroups' registers: 4 VGPRs over)
+    constexpr int kShared = std::is_same<In, odd32>::value ? kFinishBlock : kBlock;
+    if (finish && P.B > cu_count())
+        hipLaunchKernelGGL((rs_finish_kernel<In, VEC, UNR, MODE, kShared>), dim3((unsigned)P.B), dim3(kShared), 0, s,
+                           P, max_depth, out_tokens, out_len, out_status);
+    else if (finish)
+        hipLaunchKernelGGL((rs_finish_kernel<In, VEC, UNR, MODE, kFinishBlock>), dim3((unsigned)P.B),
+                           dim3(kFinishBlock), 0, s, P, max_depth, out_tokens, out_len, out_status);
     else
         hipLaunchKernelGGL((rs_decide_kernel<In, VEC, UNR, MODE>), dim3((unsigned)((int64_t)P.B * P.N)),
                            dim3(kBlock), 0, s, P);
