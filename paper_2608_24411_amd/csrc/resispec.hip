@@ -884,24 +884,30 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
             // weighs s1 plus the masses of the candidates from i on (a suffix sum, no
             // cancellation); its scale against the whole draft is st_ds[i].
             double wc = 0.0;
-            if (mask_cands && lane < nc) {
-                const int32_t x = sm.cand_tok[lane];
+            if (mask_cands) {
+                const int32_t x = lane < nc ? sm.cand_tok[lane] : -1;
                 bool first = x >= 0 && x < V;
-                for (int c = 0; c < lane; ++c) first = first && sm.cand_tok[c] != x;
-                if (first) wc = exp2((double)sm.cand_ld[lane] * c2d + (double)Kd);
+                for (int c = 0; c < (kOne ? 0 : nc); ++c)
+                    first = first && !(c < lane && __builtin_amdgcn_readlane(x, c) == x);
+                // (the holders' masses, unless the references have changed since)
+                if (first)
+                    wc = holders && !refixed ? sm.cand_q[lane]
+                                             : exp2((double)sm.cand_ld[lane] * c2d + (double)Kd);
             }
             const double sd = mask_cands ? s1 + wave_sum(wc) : s1;
             const bool ok = s0 >= kLowSum && s0 < INFINITY && (!internal || (sd >= kLowSum && sd < INFINITY));
-            if (mask_cands) {
-                double suf = 0.0;
+            if (!kOne && mask_cands) {
+                // (the sums one after another, the divisions one lane each: as one chain of
+                // both, ten candidates took 2.5 us of a row)
+                double suf = 0.0, own = 0.0;
                 for (int c = nc - 1; c >= 0; --c) {
                     suf += readlane_d(wc, c);
-                    const double rem = s1 + suf;
-                    if (lane == 0) sm.st_ds[c] = c == 0 ? 1.0 : (rem > 0.0 ? sd / rem : 0.0);
+                    own = lane == c ? suf : own;
                 }
-                if (lane == 0) sm.st_ds[nc] = s1 > 0.0 ? sd / s1 : 0.0;
-            } else if (lane == 0) {
-                for (int c = 0; c <= nc; ++c) sm.st_ds[c] = 1.0;
+                const double rem = s1 + own;
+                if (lane < nc) sm.st_ds[lane] = lane == 0 ? 1.0 : (rem > 0.0 ? sd / rem : 0.0);
+            } else if (lane < nc) {
+                sm.st_ds[lane] = 1.0;
             }
             if (lane == 0) {
                 sm.St = s0;
@@ -934,17 +940,18 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
             zero_residual_row(P, row);
             return;
         }
-        // exact maxima of both rows, then the references are taken from them
+        // exact maxima of both rows, then the references are taken from them (of a resumed
+        // row, the target's alone: it is a leaf)
         {
             float mx = -FLT_MAX, my = -FLT_MAX;
-            wave_sweep<In, VEC, UNR, true, 0, kNtPass1>(tg, dg, V, G, nl, s0, false, pre, pre, &sm.next_slot,
+            wave_sweep<In, VEC, UNR, !kOne, 0, kNtPass1>(tg, dg, V, G, nl, s0, false, pre, pre, &sm.next_slot,
                 [&](const float (&t)[UNR][VEC], const float (&d)[UNR][VEC], int, int) {
 #pragma unroll
                     for (int u = 0; u < UNR; ++u)
 #pragma unroll
                         for (int e = 0; e < VEC; ++e) {
                             mx = fmaxf(mx, t[u][e]);
-                            my = internal ? fmaxf(my, d[u][e]) : my;
+                            if (!kOne) my = internal ? fmaxf(my, d[u][e]) : my;
                         }
                 },
                 [](int) {});
