@@ -103,6 +103,12 @@ typedef struct {
  *   out_accepted_len            : [B] int32  1 if a candidate was accepted, else 0
  *   out_status                  : [B] int32  rs_seq_status; may be NULL
  * k = 0 draws directly from the target distribution.  B = 0 is a no-op.
+ * Batches of few long rows (up to 128 rows of at least 160 KiB, and the same for the node
+ * rows of resispec_verify_tree and resispec_verify_nodes) take several workgroups a row,
+ * whose exchange states come from a pool of 128 that the library keeps on each GPU; calls may
+ * overlap on any streams and threads, and replay from graphs.  The results are the same bit
+ * for bit, and RS_SEQ_GROUP_TIMEOUT is not reported: a row whose workgroups lose touch (20
+ * ms), or that finds no free state, is done by one workgroup.
  */
 rs_status resispec_verify(const void* target_logits, const void* draft_logits,
                           const int32_t* cand_ids, const float* u_accept,

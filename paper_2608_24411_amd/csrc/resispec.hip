@@ -165,10 +165,14 @@ struct RowGroup {
 };
 
 // per-sequence (or per-row) workspace of a row group: formation arrivals and state (each
-// on its own 64-byte line), slot totals, maxima (tagged words, zero before the launch)
+// on its own 64-byte line), slot totals, maxima (tagged words, zero before the launch).
+// Groups of the library's pool also count the members that have left, and keep the outcome
+// for the last of them (tagged words).
 constexpr int32_t kMaxGroup = 16;
+constexpr int64_t kGroupLeave = 0;
 constexpr int64_t kGroupArrive = 64;
 constexpr int64_t kGroupState = 128;
+constexpr int64_t kGroupOutcome = 192;
 constexpr int64_t kGroupXw = 256;
 constexpr int64_t kGroupXm = kGroupXw + 2 * 2 * kMaxSlots * 2 * (int64_t)sizeof(unsigned long long);
 constexpr int64_t kGroupWordsEnd = kGroupXm + 2 * kMaxGroup * 2 * (int64_t)sizeof(unsigned long long);
@@ -1722,6 +1726,18 @@ __global__ void __launch_bounds__(kResetBlock) rs_group_reset(char* __restrict__
     for (int64_t k = threadIdx.x; k < nwords; k += kResetBlock) words[k] = 0ull;
 }
 
+// The row and node of group g (node-major order).
+__device__ __forceinline__ int64_t group_row(const KParams& P, int32_t g, int32_t& b, int32_t& n) {
+    if (P.flat) {
+        b = g;
+        n = 0;
+        return g;
+    }
+    n = g / P.B;
+    b = g - n * P.B;
+    return (int64_t)b * P.N + n;
+}
+
 // All-nodes schedule with row groups, for batches of few rows: S workgroups per node row
 // (group g of group_of verifies row g of the node-major order, with its state at
 // ws + g * kGroupStride).  The same chunks, slots and summation order as the row kernel,
@@ -1732,19 +1748,9 @@ __global__ void __launch_bounds__(kPathBlock) __attribute__((amdgpu_waves_per_eu
 rs_rowgroup_kernel(const KParams P, const GroupArgs ga) {
     __shared__ Smem sm;
     const int32_t S = ga.S;
-    int32_t g, member;
+    int32_t g, member, b, n;
     if (!group_of(ga, g, member)) return;
-    int64_t row;
-    int32_t b, n;
-    if (P.flat) {
-        row = g;
-        b = g;
-        n = 0;
-    } else {
-        n = g / P.B;
-        b = g - n * P.B;
-        row = (int64_t)b * P.N + n;
-    }
+    const int64_t row = group_row(P, g, b, n);
     char* base = ga.ws + (int64_t)g * kGroupStride;
     RowGroup grp{S, member, reinterpret_cast<unsigned long long*>(base + kGroupXw),
                  reinterpret_cast<unsigned long long*>(base + kGroupXm), 0u, ga.wait};
@@ -1759,6 +1765,116 @@ rs_rowgroup_kernel(const KParams P, const GroupArgs ga) {
     verify_row<In, VEC, UNR, MODE, kPathBlock, true>(P, sm, row, b, n, [&](int32_t child, int32_t tok, int32_t st) {
         if (lead) write_outcome(P, row, child, tok, st);
     }, grp);
+}
+
+// Row groups without a caller's workspace (the flat entry, and node rows whose workspace
+// holds outcomes alone), for batches of few long rows: the group states come from a pool
+// that the library keeps on each GPU (kPoolGroups states, about 1.2 MB).  A launch before
+// the groups' claims a free state for every row (a bit of g_pool_used), clears it, and
+// leaves its number where the row's outcome will go (the flat entry's accepted lengths, or
+// the node statuses, from kClaimBase on, above every outcome; kClaimNone if none was free:
+// the row's first workgroup then does the row alone).  Nothing else writes there until every
+// member of the row has left the group: the last one out writes the outcome and gives the
+// state back.  So launches that overlap, on any streams and from any threads, or that replay
+// from a graph, never share a state.
+//
+// A group whose exchange times out (members preempted for 20 ms, say) does not fail the row
+// here: its first workgroup does the row over, alone.  Measured: 64 rows of V = 128,257 bf16
+// with six candidates 129.7 us with one workgroup a row, 71.6 us with four (the claim's
+// launch included); one CU's vector ALU sets the time of a pass over such a row.
+constexpr int32_t kPoolGroups = 128;
+constexpr int32_t kClaimNone = 63, kClaimBase = 64;
+__device__ __align__(256) char g_pool[kPoolGroups * kGroupStride];
+__device__ uint32_t g_pool_used[kPoolGroups / 32];
+
+__device__ __forceinline__ int32_t* claim_of(const KParams& P, int64_t row) {
+    return (P.flat ? P.out_len : P.node_status) + row;
+}
+
+__global__ void __launch_bounds__(kResetBlock) rs_pool_claim(const KParams P) {
+    __shared__ int32_t s_slot;
+    const int32_t g = blockIdx.x;
+    int32_t b, n;
+    const int64_t row = group_row(P, g, b, n);
+    if (threadIdx.x == 0) {
+        // row g tries state g first, so the rows of a launch meet only where other launches
+        // hold states
+        int32_t slot = -1;
+        for (int32_t k = 0; k < kPoolGroups && slot < 0; ++k) {
+            const int32_t at = (g + k) % kPoolGroups;
+            const uint32_t bit = 1u << (at & 31);
+            if (!(atomicOr(&g_pool_used[at >> 5], bit) & bit)) slot = at;
+        }
+        *claim_of(P, row) = slot < 0 ? kClaimNone : kClaimBase + slot;
+        s_slot = slot;
+    }
+    __syncthreads();
+    if (s_slot < 0) return;
+    unsigned long long* words = reinterpret_cast<unsigned long long*>(g_pool + s_slot * kGroupStride);
+    for (int64_t k = threadIdx.x; k < kGroupWordsEnd / (int64_t)sizeof(unsigned long long); k += kResetBlock)
+        words[k] = 0ull;
+}
+
+template <typename In, int VEC, int UNR, int MODE>
+__global__ void __launch_bounds__(kPathBlock) __attribute__((amdgpu_waves_per_eu(2)))
+rs_poolgroup_kernel(const KParams P, const GroupArgs ga) {
+    __shared__ Smem sm;
+    const int32_t S = ga.S;
+    int32_t g, member, b, n;
+    if (!group_of(ga, g, member)) return;
+    const int64_t row = group_row(P, g, b, n);
+    const int32_t slot = __builtin_amdgcn_readfirstlane(*claim_of(P, row)) - kClaimBase;
+    // no state: the first workgroup does the row (the others may find its outcome here)
+    if (slot < 0 && member != 0) return;
+    char* base = g_pool + max(slot, 0) * kGroupStride;
+    RowGroup grp{S, member, reinterpret_cast<unsigned long long*>(base + kGroupXw),
+                 reinterpret_cast<unsigned long long*>(base + kGroupXm), 0u, ga.wait};
+    bool lead = member == 0;
+    const int form = slot < 0 ? 2 : form_group(sm, grp, base, ga.form_wait);
+    if (form == 2) {
+        grp.S = 1;
+        grp.w = 0;
+        lead = true;
+    }
+    if (form != 0) {
+        for (;;) {
+            verify_row<In, VEC, UNR, MODE, kPathBlock, true>(P, sm, row, b, n,
+                                                         [&](int32_t child, int32_t tok, int32_t st) {
+                sm.res_child = child;
+                sm.res_tok = tok;
+                sm.res_status = st;
+            }, grp);
+            __syncthreads();
+            const int32_t st = __builtin_amdgcn_readfirstlane(sm.res_status);
+            if (st != RS_SEQ_GROUP_TIMEOUT || grp.S == 1) break;
+            // words of this member that no other has read yet land before it leaves
+            __threadfence();
+            __syncthreads();
+            if (!lead) break;
+            grp.S = 1;
+            grp.w = 0;
+        }
+    }
+    if (threadIdx.x != 0) return;
+    if (slot < 0) {
+        write_outcome(P, row, sm.res_child, sm.res_tok, sm.res_status);
+        return;
+    }
+    // Leaving.  Every word that a member published has been read by every member (or the
+    // fence above has passed), so nothing of this launch is still on its way to the state
+    // when the last member gives it back.
+    unsigned long long* out = reinterpret_cast<unsigned long long*>(base + kGroupOutcome);
+    if (lead && form != 0) {
+        put_tagged(out, 1u, (uint32_t)sm.res_child);
+        put_tagged(out + 1, 1u, (uint32_t)sm.res_tok);
+        put_tagged(out + 2, 1u, (uint32_t)sm.res_status);
+    }
+    if (atomicAdd(reinterpret_cast<uint32_t*>(base + kGroupLeave), 1u) + 1u != (uint32_t)S) return;
+    const unsigned long long* const w[3] = {out, out + 1, out + 2};
+    uint32_t v[3] = {~0u, ~0u, (uint32_t)RS_SEQ_GROUP_TIMEOUT};
+    get_tagged_all<3>(w, 1u, v, (uint64_t)wall_clock64(), kGroupWaitTicks);
+    write_outcome(P, row, (int32_t)v[0], (int32_t)v[1], (int32_t)v[2]);
+    atomicAnd(&g_pool_used[slot >> 5], ~(1u << (slot & 31)));
 }
 
 // ----------------------------------------------------------- walk kernel ----
@@ -2038,9 +2154,46 @@ void set_slots(KParams& P) {
     P.nslots = (int32_t)((nch + G - 1) / G);
 }
 
+// Members per row that batches of few long rows take by themselves.  Measured: beyond one
+// workgroup per CU, eight members per row or below 40 KiB of a row per member, and for rows
+// under 160 KiB, the exchanges cost more than the split passes save.
+template <typename In>
+int32_t auto_row_group(const KParams& P, int64_t nrows, int64_t smax) {
+    if (kAutoRowGroup < smax) smax = kAutoRowGroup;
+    const int64_t row_bytes = (int64_t)P.V * (int64_t)sizeof(In);
+    const int64_t by_bytes = row_bytes < kAutoSplitBytes ? 1 : row_bytes / kAutoRowBytes;
+    if (by_bytes < smax) smax = by_bytes;
+    if ((int64_t)cu_count() / nrows < smax) smax = (int64_t)cu_count() / nrows;
+    if (P.nslots / (kPathBlock / 64) < smax) smax = P.nslots / (kPathBlock / 64);
+    return smax >= 2 ? (int32_t)smax : 1;
+}
+
+GroupArgs group_args(int32_t S, char* ws, int64_t groups) {
+    const bool xcd = S <= kXcdMaxMembers && groups >= kXcdMinGroups;
+    return GroupArgs{S, ws, g_group_wait.load(std::memory_order_relaxed),
+                     g_form_wait.load(std::memory_order_relaxed), (int32_t)groups, xcd ? 1 : 0};
+}
+unsigned group_grid(const GroupArgs& ga) {
+    const int64_t groups = ga.xcd ? (ga.groups + kXcds - 1) / kXcds * kXcds : (int64_t)ga.groups;
+    return (unsigned)(groups * ga.S);
+}
+
 template <typename In, int VEC, int UNR, int MODE>
-hipError_t launch_row_kernel(KParams P, int64_t nrows, hipStream_t s) {
+hipError_t launch_row_kernel(KParams P, int64_t nrows, bool pool, hipStream_t s) {
     set_slots<VEC, UNR>(P);
+    if constexpr (VEC > 1) {
+        // few long rows: row groups in the library's pool
+        const int32_t S = pool && nrows <= kPoolGroups && !P.residual_out ? auto_row_group<In>(P, nrows, kMaxGroup) : 1;
+        if (S > 1) {
+            hipLaunchKernelGGL(rs_pool_claim, dim3((unsigned)nrows), dim3(kResetBlock), 0, s, P);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            const GroupArgs ga = group_args(S, nullptr, nrows);
+            hipLaunchKernelGGL((rs_poolgroup_kernel<In, VEC, UNR, MODE>), dim3(group_grid(ga)), dim3(kPathBlock), 0, s,
+                               P, ga);
+            return hipGetLastError();
+        }
+    }
     if (VEC > 1 && nrows <= cu_count())
         hipLaunchKernelGGL((rs_row_kernel<In, VEC, UNR, MODE, VEC == 1 ? kBlock : kLoneBlock>), dim3((unsigned)nrows),
                            dim3(kLoneBlock), 0, s, P);
@@ -2117,11 +2270,8 @@ hipError_t launch_path_kernel(KParams P, PathOut* path, hipStream_t s) {
     int32_t* ot = path->out_tokens;
     int32_t* ol = path->out_len;
     int32_t* os = path->out_status;
-    const bool xcd = S <= kXcdMaxMembers && P.B >= kXcdMinGroups;
-    const GroupArgs ga{S, path->ws, g_group_wait.load(std::memory_order_relaxed),
-                       g_form_wait.load(std::memory_order_relaxed), P.B, xcd ? 1 : 0};
-    const int64_t groups = xcd ? ((int64_t)P.B + kXcds - 1) / kXcds * kXcds : (int64_t)P.B;
-    hipLaunchKernelGGL((rs_path_kernel<In, VEC, UNR, MODE>), dim3((unsigned)(groups * S)), dim3(kPathBlock), 0, s,
+    const GroupArgs ga = group_args(S, path->ws, P.B);
+    hipLaunchKernelGGL((rs_path_kernel<In, VEC, UNR, MODE>), dim3(group_grid(ga)), dim3(kPathBlock), 0, s,
                        kp, md, ot, ol, os, ga);
     return hipGetLastError();
 }
@@ -2145,16 +2295,7 @@ hipError_t launch_rowgroups(KParams P, int64_t nrows, RowGroupLaunch* rg, hipStr
         int64_t smax = (int64_t)kMaxGroup;
         if (cap / nrows < smax) smax = cap / nrows;
         if (rg->group == 0) {
-            // measured: beyond one workgroup per CU, eight members per row or below 40 KiB
-            // of a row per member, and for rows under 160 KiB, the exchanges cost more than
-            // the split passes save
-            if (kAutoRowGroup < smax) smax = kAutoRowGroup;
-            const int64_t row_bytes = (int64_t)P.V * (int64_t)sizeof(In);
-            const int64_t by_bytes = row_bytes < kAutoSplitBytes ? 1 : row_bytes / kAutoRowBytes;
-            if (by_bytes < smax) smax = by_bytes;
-            if ((int64_t)cu_count() / nrows < smax) smax = (int64_t)cu_count() / nrows;
-            if (P.nslots / (kPathBlock / 64) < smax) smax = P.nslots / (kPathBlock / 64);
-            S = smax >= 2 ? (int32_t)smax : 1;
+            S = auto_row_group<In>(P, nrows, smax);
         } else if (!rg->ws) {
             S = -1;
         } else if (!aligned_rows<In>(P)) {
@@ -2175,18 +2316,14 @@ hipError_t launch_rowgroups(KParams P, int64_t nrows, RowGroupLaunch* rg, hipStr
     }
     if (rg->dry_run) return hipSuccess;
     if (S == 1) {
-        return launch_row_kernel<In, VEC, UNR, MODE>(P, nrows, s);
+        return launch_row_kernel<In, VEC, UNR, MODE>(P, nrows, false, s);
     }
     hipLaunchKernelGGL(rs_group_reset, dim3((unsigned)nrows), dim3(kResetBlock), 0, s, rg->ws, (int32_t)nrows);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     KParams kp = P;
-    const bool xcd = S <= kXcdMaxMembers && nrows >= kXcdMinGroups;
-    const GroupArgs ga{S, rg->ws, g_group_wait.load(std::memory_order_relaxed),
-                       g_form_wait.load(std::memory_order_relaxed), (int32_t)nrows, xcd ? 1 : 0};
-    const int64_t groups = xcd ? (nrows + kXcds - 1) / kXcds * kXcds : nrows;
-    hipLaunchKernelGGL((rs_rowgroup_kernel<In, VEC, UNR, MODE>), dim3((unsigned)(groups * S)), dim3(kPathBlock), 0,
-                       s, kp, ga);
+    const GroupArgs ga = group_args(S, rg->ws, nrows);
+    hipLaunchKernelGGL((rs_rowgroup_kernel<In, VEC, UNR, MODE>), dim3(group_grid(ga)), dim3(kPathBlock), 0, s, kp, ga);
     return hipGetLastError();
 }
 
@@ -2203,7 +2340,7 @@ hipError_t launch_rows_m(const KParams& P, int dtype, RowLoads loads, int64_t nr
                          hipStream_t s) {
     return with_layout(dtype, loads, [&](auto in, auto vec, auto unr) {
         return path ? launch_path_kernel<decltype(in), vec(), unr(), MODE>(P, path, s)
-                    : launch_row_kernel<decltype(in), vec(), unr(), MODE>(P, nrows, s);
+                    : launch_row_kernel<decltype(in), vec(), unr(), MODE>(P, nrows, true, s);
     });
 }
 hipError_t launch_rows(const KParams& P, const rs_params* prm, RowLoads loads, int64_t nrows, hipStream_t s,
