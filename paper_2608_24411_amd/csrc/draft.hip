@@ -53,6 +53,16 @@ struct DParams {
 // 77 KB.  While a row's draws leave one wave running (draws without replacement, or a
 // single child), the other waves' registers and the small LDS let further rows'
 // workgroups start on the CU and stream.
+// Slots of a draft row: twice the verification kernels', so a slot is one chunk up to
+// V = 262,144 (bf16) or 131,072 (fp32), and a draw re-reads and sums 16 or 8 elements a lane.
+// Half of a draw's time is that slot's arithmetic on one wave, draw after draw without
+// replacement.  Measured: 256 serving trees (V = 151,936 bf16, ten sequential draws at every
+// root) 93.1 us with 128 slots, 82.3 us with 256; slots of half a chunk (512 slots) 86.7 us,
+// their sums cost the pass more than the draws gain, and ordinary loads in the pass, for the
+// slots' sake, 89.6 us.
+constexpr int kDraftSlots = 2 * kMaxSlots;
+constexpr int kLaneSlots = kDraftSlots / 64;   // slot totals a lane holds
+
 struct DraftSmem {
     int32_t decision;
     int32_t next_slot;
@@ -63,7 +73,7 @@ struct DraftSmem {
     int32_t cand_node[kMaxCand];
     float cand_u[kMaxCand];
     float wmax[2][kMaxWaves];
-    double slotA[kMaxSlots];
+    double slotA[kDraftSlots];
 };
 
 // Four waves per row workgroup (the verification kernels take eight): a row's draws
@@ -230,14 +240,14 @@ __global__ void __launch_bounds__(kDraftBlock) __attribute__((amdgpu_waves_per_e
     const bool worep = P.worep != 0;
     if (worep && wid != 0) return;
     const int R = G * VEC * UNR;          // elements of a slot per lane
-    // slot totals in vocabulary order, lane l holding slots 4l .. 4l+3.  Without
+    // slot totals in vocabulary order, lane l holding kLaneSlots of them.  Without
     // replacement a draw replaces its slot's total by the fp64 sum of the slot's elements
     // that remain (computed in the draw below), so the mass left is always a sum of
     // what remains, never the total less the removed mass.
-    double Ts[4];
+    double Ts[kLaneSlots];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int s2 = 4 * lane + q;
+    for (int q = 0; q < kLaneSlots; ++q) {
+        const int s2 = kLaneSlots * lane + q;
         Ts[q] = s2 < nslots ? sm.slotA[s2] : 0.0;
     }
     for (int i = worep ? 0 : wid; i < nc; i += worep ? 1 : kWaves) {
@@ -246,7 +256,7 @@ __global__ void __launch_bounds__(kDraftBlock) __attribute__((amdgpu_waves_per_e
         const int rslot = rtok >= 0 ? (rtok / CHUNK) / G : -1;
         double own = 0.0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) own += Ts[q];
+        for (int q = 0; q < kLaneSlots; ++q) own += Ts[q];
         const double incl = wave_incl_scan(own, lane);
         const double excl = incl - own;
         const double thr = (double)sm.cand_u[i] * readlane_d(incl, 63);
@@ -263,13 +273,13 @@ __global__ void __launch_bounds__(kDraftBlock) __attribute__((amdgpu_waves_per_e
             int lastpos = -1;
             double lastbase = 0.0;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < kLaneSlots; ++q) {
                 if (Ts[q] > 0.0) {
                     if (ks < 0 && c + Ts[q] > thr) {
-                        ks = 4 * lane + q;
+                        ks = kLaneSlots * lane + q;
                         base = c;
                     }
-                    lastpos = 4 * lane + q;
+                    lastpos = kLaneSlots * lane + q;
                     lastbase = c;
                 }
                 c += Ts[q];
@@ -297,7 +307,7 @@ __global__ void __launch_bounds__(kDraftBlock) __attribute__((amdgpu_waves_per_e
                 }
                 return v;
             };
-            constexpr int kRegRun = 32;
+            constexpr int kRegRun = 16;
             float vals[kRegRun];
             double own2 = 0.0;
             const bool inreg = R <= kRegRun;
@@ -393,8 +403,8 @@ __global__ void __launch_bounds__(kDraftBlock) __attribute__((amdgpu_waves_per_e
                 const bool mine = tok >= t0 && tok < t0 + R;
                 const double rest = wave_sum(own2 - (mine ? tval : 0.0));
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (4 * lane + q == ks) Ts[q] = rest > 0.0 ? rest : 0.0;
+                for (int q = 0; q < kLaneSlots; ++q)
+                    if (kLaneSlots * lane + q == ks) Ts[q] = rest > 0.0 ? rest : 0.0;
             }
         }
         if (lane == 0) {
@@ -414,7 +424,7 @@ template <typename In, int VEC, int UNR>
 hipError_t launch_draft_t(DParams P, hipStream_t s) {
     constexpr int64_t CHUNK = 64 * VEC * UNR;
     const int64_t nch = ((int64_t)P.V + CHUNK - 1) / CHUNK;
-    const int64_t G = (nch + kMaxSlots - 1) / kMaxSlots;
+    const int64_t G = (nch + kDraftSlots - 1) / kDraftSlots;
     P.G = (int32_t)G;
     P.nslots = (int32_t)((nch + G - 1) / G);
     hipLaunchKernelGGL((rs_draft_kernel<In, VEC, UNR>), dim3((unsigned)((int64_t)P.B * P.N)), dim3(kDraftBlock), 0,
