@@ -168,7 +168,7 @@ def _dev(t, dtype, name):
 
 
 def _shape(t, shape, name):
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape and tuple(t.shape) != tuple(shape):
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
 
 
@@ -191,9 +191,15 @@ def _check_tree_shapes(target_logits, draft_logits, node_token, parent, u_accept
 
 
 def _stream(stream):
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    # the current stream's handle, without the Stream object that current_stream() makes
+    # around it (2.8 us of a 15.7 us call)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(raw(torch.cuda.current_device()))
 
 
 def _check(st):
