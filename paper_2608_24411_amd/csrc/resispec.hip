@@ -466,6 +466,13 @@ __device__ __forceinline__ void keep_slot_totals(const KParams& P, const Smem& s
     }
 }
 
+// One node of the sequence's tree per thread, for the path schedule: its walk reads the tree
+// once (trees of no more nodes than threads) instead of at every row.
+struct HeldNode {
+    int32_t parent, token;
+    float u;
+};
+
 // One node row's verification (the steps of Algorithm 1 at one node, or its bonus draw).
 // RC: the path schedule, whose later ResiSpec rejection passes keep the row's residual
 // in P.rcache when the caller's workspace holds it (see the rejection passes below).
@@ -474,7 +481,7 @@ template <typename In, int VEC, int UNR, int MODE, int BLK, bool SPLIT, bool RC 
           int SCHED = kSchedAll, typename Emit>
 __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int64_t row,
                                            const int32_t b, const int32_t n, Emit&& emit,
-                                           RowGroup& grp) {
+                                           RowGroup& grp, const HeldNode held = HeldNode{}) {
     constexpr int kBlock = BLK;
     constexpr int kWaves = BLK / 64;
     const int tid = threadIdx.x;
@@ -580,6 +587,16 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
     bool holder = false;
     int32_t hx = 0, hnode = 0, hrank = 0;
     float hu = 0.0f;
+    // A holder's two logits are requested as soon as its token is known, before the wait for
+    // the first chunk, and used after it (requested after that wait, their latency came on
+    // top: the benchmarked deferred step took 329 us, now 320).
+    In raw_t{}, raw_d{};
+    auto gather = [&]() {
+        if (holder && hx >= 0 && hx < V) {
+            raw_t = tg[hx];
+            raw_d = dg[hx];
+        }
+    };
     int nc = 0;
     int status = RS_SEQ_OK;
     if (P.flat) {
@@ -591,19 +608,21 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
             hrank = tid;
         }
         nc = P.k;
+        gather();
         publish_premax();
         __syncthreads();
     } else if (P.N <= kBlock) {
         const int64_t sb = (int64_t)b * P.N;
         int bad = 0;
         if (tid < P.N) {
-            const int32_t pm = P.parent[sb + tid];
-            hx = P.node_token[sb + tid];
-            hu = P.ua[sb + tid];
+            const int32_t pm = RC ? held.parent : P.parent[sb + tid];
+            hx = RC ? held.token : P.node_token[sb + tid];
+            hu = RC ? held.u : P.ua[sb + tid];
             hnode = tid;
             bad = (tid == 0) ? (pm != -1) : (pm < 0 || pm >= tid);
             holder = tid > n && pm == n;
         }
+        gather();
         const uint64_t cm = __ballot(holder);
         const uint64_t bm = __ballot(bad);
         hrank = __popcll(cm & __lanemask_lt());
@@ -682,12 +701,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
         return;
     }
     if (tid == 0) sm.status = RS_SEQ_OK;
-    // candidate logits (their latency overlaps the first chunk's)
-    float hlt = 0.0f, hld = 0.0f;
-    if (holder && hrank < kMaxCand && hx >= 0 && hx < V) {
-        hlt = widen(tg[hx]);
-        hld = widen(dg[hx]);
-    }
+    const float hlt = widen(raw_t), hld = widen(raw_d);   // 0 where there is no candidate
 
     const bool internal = nc > 0;
     if constexpr (SCHED == kSchedDecide) {
@@ -1664,13 +1678,19 @@ rs_path_kernel(const KParams P, int32_t max_depth, int32_t* __restrict__ out_tok
     if (lead)
         for (int64_t i = tid; i < W; i += kBlock) out[i] = -1;
     int32_t n = 0, len = 0, status = RS_SEQ_OK;
+    HeldNode held{};
+    if (tid < N && N <= kBlock) {
+        held.parent = P.parent[(int64_t)b * N + tid];
+        held.token = P.node_token[(int64_t)b * N + tid];
+        held.u = P.ua[(int64_t)b * N + tid];
+    }
     for (int32_t steps = 0; steps <= N; ++steps) {
         verify_row<In, VEC, UNR, MODE, kBlock, true, true>(P, sm, (int64_t)b * N + n, b, n,
                                                      [&](int32_t child, int32_t tok, int32_t st) {
             sm.res_child = child;
             sm.res_tok = tok;
             sm.res_status = st;
-        }, grp);
+        }, grp, held);
         __syncthreads();
         const int32_t st = __builtin_amdgcn_readfirstlane(sm.res_status);
         const int32_t c = __builtin_amdgcn_readfirstlane(sm.res_child);
