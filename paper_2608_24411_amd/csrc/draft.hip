@@ -48,11 +48,6 @@ struct DParams {
     int32_t G, nslots;
 };
 
-// The draft kernel's shared state: one fp64 total per slot (the wave that sweeps a slot
-// sums its lanes' partials itself), so about 2 KB instead of the verification kernels'
-// 77 KB.  While a row's draws leave one wave running (draws without replacement, or a
-// single child), the other waves' registers and the small LDS let further rows'
-// workgroups start on the CU and stream.
 // Slots of a draft row: twice the verification kernels', so a slot is one chunk up to
 // V = 262,144 (bf16) or 131,072 (fp32), and a draw re-reads and sums 16 or 8 elements a lane.
 // Half of a draw's time is that slot's arithmetic on one wave, draw after draw without
@@ -63,6 +58,11 @@ struct DParams {
 constexpr int kDraftSlots = 2 * kMaxSlots;
 constexpr int kLaneSlots = kDraftSlots / 64;   // slot totals a lane holds
 
+// The draft kernel's shared state: one fp64 total per slot (the wave that sweeps a slot
+// sums its lanes' partials itself), so about 3 KB instead of the verification kernels'
+// 77 KB.  While a row's draws leave one wave running (draws without replacement, or a
+// single child), the other waves' registers and the small LDS let further rows'
+// workgroups start on the CU and stream.
 struct DraftSmem {
     int32_t decision;
     int32_t next_slot;
