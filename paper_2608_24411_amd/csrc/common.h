@@ -33,6 +33,34 @@ constexpr bool kNtPass1 = false;
 constexpr bool kNtRej = true;
 constexpr bool kNtLeaf = true;
 constexpr int kMaxSlots = 128;           // per-row slots (runs of chunks) with partial sums
+
+// A row of V elements in chunks of 64 * VEC * UNR, grouped into at most kMaxSlots slots of G
+// chunks.  The passes visit every chunk of every slot; those of the last slot that start past
+// the row read as -inf.
+struct SlotLayout {
+    int32_t G, nslots;
+};
+template <int VEC, int UNR>
+constexpr SlotLayout slot_layout(int64_t V) {
+    constexpr int64_t CHUNK = 64 * VEC * UNR;
+    const int64_t nch = (V + CHUNK - 1) / CHUNK;
+    const int64_t G = (nch + kMaxSlots - 1) / kMaxSlots;
+    return {(int32_t)G, (int32_t)((nch + G - 1) / G)};
+}
+
+// The path schedule's residual cache holds rc_half(V) elements each of R and Q per sequence:
+// the row, padded to whole chunks of every layout (all divide kRcPad; the 16-byte accesses
+// stay aligned with it), and so not the chunks that start past the row: those are not held.
+// c0: a chunk's (or one of its loads') first element.
+constexpr int64_t kRcPad = 1024;
+constexpr int64_t rc_half(int64_t V) { return (V + kRcPad - 1) / kRcPad * kRcPad; }
+__host__ __device__ constexpr bool rc_holds(int c0, int half) { return c0 < half; }
+// The chunks of slot s that are held: its first ones, and one at least (a slot's first chunk
+// starts inside the row).
+__host__ __device__ constexpr int rc_slot_chunks(int s, int G, int chunk, int half) {
+    return half / chunk - s * G < G ? half / chunk - s * G : G;
+}
+
 // A row's exponent reference is fixed before pass 1; sums outside [2^-kLow, inf) send the
 // row through an exact-maximum pass and a second pass 1.
 constexpr double kLowSum = 1.0 / 1048576.0;

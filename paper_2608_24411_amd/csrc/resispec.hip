@@ -323,11 +323,11 @@ __device__ __forceinline__ bool pass_totals(Smem& sm, RowGroup& grp, int nslots,
 }
 
 // Residual cache of the path schedule: two fp32 values per element of a row (the residual
-// and the unnormalised draft mass), each at the element's index in a per-sequence array
-// padded to a multiple of kRcPad elements (so every chunk of every layout lies inside it
-// and the 16-byte accesses stay aligned).  A lane reads and writes the same VEC
-// consecutive elements it takes from the logits rows.
-constexpr int64_t kRcPad = 1024;
+// and the unnormalised draft mass), each at the element's index in a per-sequence array of
+// rc_half(V) elements.  A lane reads and writes the same VEC consecutive elements it takes
+// from the logits rows.  The last slot of a row may have chunks past the row (where the
+// number of chunks is no multiple of the slot's); rc_holds tells them apart: they are
+// neither stored nor summed (their logits, -inf, would add zeros).
 
 template <int VEC>
 __device__ __forceinline__ void rc_load(const float* __restrict__ p, float (&v)[VEC]) {
@@ -362,18 +362,16 @@ __device__ __forceinline__ void rc_store(float* __restrict__ p, const float (&v)
 // processed; units are processed in the order they are requested.  body(r, q, i0, slot,
 // u) gets R (which it may overwrite) and Q of unit u of a chunk (element e has index
 // i0 + e); chunk_end(slot) runs after a chunk's last unit and flush(slot) after a slot's
-// last chunk.
+// last chunk.  Chunks that the cache (half elements each of R and Q) does not hold are left
+// out.
 template <int VEC, int UNR, typename Body, typename ChunkEnd, typename Flush>
-__device__ __forceinline__ void wave_sweep_rc(const float* __restrict__ rc, const float* __restrict__ qc, int G,
-                                              int nslots, int sbase, bool reverse, int* counter, Body&& body,
+__device__ __forceinline__ void wave_sweep_rc(const float* __restrict__ rc, const float* __restrict__ qc, int half,
+                                              int G, int nslots, int sbase, bool reverse, int* counter, Body&& body,
                                               ChunkEnd&& chunk_end, Flush&& flush) {
     constexpr int CHUNK = 64 * VEC * UNR;
     const int lane = threadIdx.x & 63;
     const int wid = threadIdx.x >> 6;
     const int lane0 = lane * VEC;
-    auto chunk_start = [&](int slot, int j) -> int {
-        return (slot * G + (reverse ? G - 1 - j : j)) * CHUNK;
-    };
     int slot = wid < nslots ? sbase + (reverse ? nslots - 1 - wid : wid) : -1;
     if (slot < 0) return;
     auto take = [&]() -> int {
@@ -383,20 +381,28 @@ __device__ __forceinline__ void wave_sweep_rc(const float* __restrict__ rc, cons
         return v < nslots ? sbase + (reverse ? nslots - 1 - v : v) : -1;
     };
     int ahead = take();
-    // a unit is (slot, chunk j of the slot, load u of the chunk); slot -1: none left
+    // a unit is (slot, chunk c of the row, load u of the chunk, chunks left in the slot after
+    // c); slot -1: none left
     struct Unit {
-        int s, j, u;
+        int s, c, u, left;
+    };
+    auto first = [&](int s) -> Unit {
+        const int n = rc_slot_chunks(s, G, CHUNK, half);
+        return Unit{s, s * G + (reverse ? n - 1 : 0), 0, n - 1};
     };
     auto next = [&](Unit x) -> Unit {
         if (++x.u < UNR) return x;
         x.u = 0;
-        if (++x.j < G) return x;
-        x.j = 0;
+        x.c += reverse ? -1 : 1;
+        if (--x.left >= 0) return x;
         x.s = ahead;
-        if (x.s >= 0) ahead = take();
+        if (x.s >= 0) {
+            ahead = take();
+            x = first(x.s);
+        }
         return x;
     };
-    auto index = [&](const Unit& x) -> int { return chunk_start(x.s, x.j) + lane0 + x.u * 64 * VEC; };
+    auto index = [&](const Unit& x) -> int { return x.c * CHUNK + lane0 + x.u * 64 * VEC; };
     auto load = [&](const Unit& x, float (&r)[VEC], float (&q)[VEC]) {
         const int i0 = index(x);
         rc_load<VEC>(rc + i0, r);
@@ -406,12 +412,12 @@ __device__ __forceinline__ void wave_sweep_rc(const float* __restrict__ rc, cons
         body(r, q, index(x), x.s, x.u);
         if (x.u == UNR - 1) {
             chunk_end(x.s);
-            if (x.j == G - 1) flush(x.s);
+            if (x.left == 0) flush(x.s);
         }
     };
     float r0[VEC], r1[VEC], r2[VEC], r3[VEC];
     float q0[VEC], q1[VEC], q2[VEC], q3[VEC];
-    Unit x0{slot, 0, 0};
+    Unit x0 = first(slot);
     load(x0, r0, q0);
     Unit last = x0;
     auto refill = [&](Unit& x, float (&r)[VEC], float (&q)[VEC]) {
@@ -1132,7 +1138,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                 const float kc = sm.st_kc[ii - 1], k1 = sm.st_k1[ii - 1], inv = sm.st_i[ii - 1];
                 const int xp = sm.st_x[ii - 1];
                 const bool keep = ii + 1 < nc;
-                const int64_t rcq = P.rc_stride / 2;   // Q's half of the sequence's cache
+                const int rcq = (int)(P.rc_stride / 2);   // Q's half of the sequence's cache
                 // one load's elements (u) at a time; the sums add them in the chain's order
                 auto step = [&](float (&R)[VEC], const float (&Q)[VEC], int i0, bool hit, float& fa, float& fb) {
 #pragma unroll
@@ -1142,8 +1148,11 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                         for (int e = 0; e < VEC; ++e)
                             if (i0 + e == xp) R[e] = 0.0f;
                     }
-                    if (keep) rc_store<VEC>(rc + i0, R);
-                    if (keep && ii == 1) rc_store<VEC>(rc + rcq + i0, Q);
+                    // (the first of these passes visits chunks past the cache)
+                    if (keep && (ii > 1 || rc_holds(__builtin_amdgcn_readfirstlane(i0), rcq))) {
+                        rc_store<VEC>(rc + i0, R);
+                        if (ii == 1) rc_store<VEC>(rc + rcq + i0, Q);
+                    }
                     if (hit) {
 #pragma unroll
                         for (int e = 0; e < VEC; ++e)
@@ -1178,7 +1187,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
                     // the chunk's sums run across its units in the order above
                     float fa = 0.0f, fb = 0.0f;
                     bool hit = false;   // the chunk's slot holds a rejected token (read at its first unit)
-                    wave_sweep_rc<VEC, UNR>(rc, rc + rcq, G, nl, s0, reverse, &sm.next_slot,
+                    wave_sweep_rc<VEC, UNR>(rc, rc + rcq, rcq, G, nl, s0, reverse, &sm.next_slot,
                         [&](float (&r)[VEC], const float (&q)[VEC], int i0, int slot, int u) {
                             if (u == 0) hit = slot_hit(slot);
                             step(r, q, i0, hit, fa, fb);
@@ -2176,14 +2185,11 @@ struct PathOut {
     int unsupported;     // out: the requested group size cannot run on this device
 };
 
-// chunks of 64 * VEC * UNR elements, grouped into at most kMaxSlots slots of G chunks
 template <int VEC, int UNR>
 void set_slots(KParams& P) {
-    constexpr int64_t CHUNK = 64 * VEC * UNR;
-    const int64_t nch = ((int64_t)P.V + CHUNK - 1) / CHUNK;
-    const int64_t G = (nch + kMaxSlots - 1) / kMaxSlots;
-    P.G = (int32_t)G;
-    P.nslots = (int32_t)((nch + G - 1) / G);
+    const SlotLayout l = slot_layout<VEC, UNR>(P.V);
+    P.G = l.G;
+    P.nslots = l.nslots;
 }
 
 // Members per row that batches of few long rows take by themselves.  Measured: beyond one
@@ -2244,8 +2250,7 @@ bool aligned_rows(const KParams& P) {
     return (int64_t)P.V * (int64_t)sizeof(In) % 16 == 0 && aligned16(P.tgt) && aligned16(P.dft);
 }
 int32_t small_chunk_slots(int32_t V) {
-    const int64_t nch = ((int64_t)V + 255) / 256, G = (nch + kMaxSlots - 1) / kMaxSlots;
-    return (int32_t)((nch + G - 1) / G);
+    return slot_layout<1, 4>(V).nslots;
 }
 
 // Members per sequence: at most as many workgroups as the device holds at once (a group
@@ -2691,9 +2696,9 @@ int32_t resispec_tree_group_size(int32_t B, int32_t N, int32_t V, const rs_param
 
 // Path workspace: one group state per sequence, then the residual cache (rc_stride(V)
 // floats per sequence, starting on a 256-byte boundary: the residual R, then the draft
-// masses Q, each V rounded up to a multiple of kRcPad).
+// masses Q, rc_half(V) elements each).
 static size_t path_states_bytes(int32_t B) { return ((size_t)B * (size_t)kGroupStride + 255) & ~(size_t)255; }
-static int64_t rc_stride(int32_t V) { return 2 * (((int64_t)V + kRcPad - 1) / kRcPad * kRcPad); }
+static int64_t rc_stride(int32_t V) { return 2 * rc_half(V); }
 
 static rs_status verify_tree_path_impl(const void* target_logits, const void* draft_logits,
                                        const int32_t* node_token, const int32_t* parent,
