@@ -31,7 +31,10 @@
  *     multiple of 16 and whose base pointer is 16-byte aligned take the
  *     vectorised path; any other V or alignment is handled element by element.
  *   - Uniforms are fp32 in [0, 1).  The accept test is strict: u < ratio.
- *   - Thread safety: calls are stateless and re-entrant.
+ *   - Thread safety: calls are re-entrant.  What the library keeps on each GPU between
+ *     calls, the pool of resispec_verify below and the scratch of
+ *     resispec_verify_tree_noalloc, does not affect results (the latter's calls must not
+ *     overlap).
  */
 #ifndef RESISPEC_H
 #define RESISPEC_H
@@ -107,8 +110,9 @@ typedef struct {
  * rows of resispec_verify_tree and resispec_verify_nodes) take several workgroups a row,
  * whose exchange states come from a pool of 128 that the library keeps on each GPU; calls may
  * overlap on any streams and threads, and replay from graphs.  The results are the same bit
- * for bit, and RS_SEQ_GROUP_TIMEOUT is not reported: a row whose workgroups lose touch (20
- * ms), or that finds no free state, is done by one workgroup.
+ * for bit, outputs are written with the outcomes and not before, and RS_SEQ_GROUP_TIMEOUT is
+ * not reported: a row whose workgroups lose touch (20 ms), or a call that meets another's
+ * states, is done by one workgroup a row.
  */
 rs_status resispec_verify(const void* target_logits, const void* draft_logits,
                           const int32_t* cand_ids, const float* u_accept,
@@ -334,6 +338,11 @@ int32_t resispec_tree_group_size(int32_t B, int32_t N, int32_t V, const rs_param
  *                     0 makes nearly every group fall back to one workgroup
  * Not for concurrent use with launches on other threads.  Always RS_OK. */
 rs_status resispec_debug_set_group_waits(uint64_t barrier_ticks, uint64_t formation_ticks);
+
+/* Testing hook: how many of the pool's group states (resispec_verify, above) are in use on
+ * the current device once it has been synchronised, which the call does; 0 unless something
+ * went wrong, -1 for a HIP error. */
+int32_t resispec_debug_pool_held(void);
 
 /* Workspace bytes resispec_verify_tree_path_group needs for B sequences of V-element rows
  * (0 if B <= 0, V <= 0 or V > RS_MAX_VOCAB): one row-group state per sequence, then two

@@ -166,13 +166,13 @@ struct RowGroup {
 
 // per-sequence (or per-row) workspace of a row group: formation arrivals and state (each
 // on its own 64-byte line), slot totals, maxima (tagged words, zero before the launch).
-// Groups of the library's pool also count the members that have left, and keep the outcome
-// for the last of them (tagged words).
+// States of the library's pool also count the members that have left, and the exchanges of
+// earlier launches.
 constexpr int32_t kMaxGroup = 16;
 constexpr int64_t kGroupLeave = 0;
 constexpr int64_t kGroupArrive = 64;
 constexpr int64_t kGroupState = 128;
-constexpr int64_t kGroupOutcome = 192;
+constexpr int64_t kGroupEpoch = 192;
 constexpr int64_t kGroupXw = 256;
 constexpr int64_t kGroupXm = kGroupXw + 2 * 2 * kMaxSlots * 2 * (int64_t)sizeof(unsigned long long);
 constexpr int64_t kGroupWordsEnd = kGroupXm + 2 * kMaxGroup * 2 * (int64_t)sizeof(unsigned long long);
@@ -230,18 +230,21 @@ __device__ __forceinline__ double join_halves(uint32_t lo, uint32_t hi) {
 // itself, and members that find it claimed leave.  The state moves once, from open to
 // formed or claimed: when formed, every member is running and takes part in every exchange.
 // Returns 1 (formed: work as member w of S), 2 (claimed: do all of it alone) or 0
-// (leave).
+// (leave).  ticket (groups of the library's pool): the member's place in the group, id while
+// it is to be taken; a member that does not find it is no part of a group: 3.
 constexpr uint32_t kFormOpen = 0u, kFormed = 1u, kFormClaimed = 2u;
 constexpr uint64_t kFormWaitTicks = 2000ull;
 
-__device__ __forceinline__ int form_group(Smem& sm, const RowGroup& g, char* base, uint64_t wait) {
+__device__ __forceinline__ int form_group(Smem& sm, const RowGroup& g, char* base, uint64_t wait,
+                                          unsigned long long* ticket = nullptr, unsigned long long id = 0ull) {
     if (threadIdx.x == 0) {
         uint32_t* arrive = reinterpret_cast<uint32_t*>(base + kGroupArrive);
         uint32_t* state = reinterpret_cast<uint32_t*>(base + kGroupState);
-        if (atomicAdd(arrive, 1u) + 1u == (uint32_t)g.S) atomicCAS(state, kFormOpen, kFormed);
+        const bool member = !ticket || atomicCAS(ticket, id, 0ull) == id;
+        if (member && atomicAdd(arrive, 1u) + 1u == (uint32_t)g.S) atomicCAS(state, kFormOpen, kFormed);
         const uint64_t t0 = (uint64_t)wall_clock64();
-        int res;
-        for (;;) {
+        int res = 3;
+        while (member) {
             const uint32_t st = __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (st != kFormOpen) {
                 res = st == kFormed ? 1 : 0;
@@ -1810,72 +1813,96 @@ rs_rowgroup_kernel(const KParams P, const GroupArgs ga) {
 
 // Row groups without a caller's workspace (the flat entry, and node rows whose workspace
 // holds outcomes alone), for batches of few long rows: the group states come from a pool
-// that the library keeps on each GPU (kPoolGroups states, about 1.2 MB).  A launch before
-// the groups' claims a free state for every row (a bit of g_pool_used), clears it, and
-// leaves its number where the row's outcome will go (the flat entry's accepted lengths, or
-// the node statuses, from kClaimBase on, above every outcome; kClaimNone if none was free:
-// the row's first workgroup then does the row alone).  Nothing else writes there until every
-// member of the row has left the group: the last one out writes the outcome and gives the
-// state back.  So launches that overlap, on any streams and from any threads, or that replay
-// from a graph, never share a state.
+// that the library keeps on each GPU (kPoolGroups states, about 1.2 MB).  Row g of a launch
+// uses state (base + g) % kPoolGroups, or none.  A launch before the groups' takes all of
+// the launch's states, by its number in the states' owner words (0: free), and lays out a ticket for
+// every member; or, where another launch has one of them, takes none, and the first
+// workgroup of every row does the row alone.  Numbers and bases are given out on the host,
+// one to a call, and a ticket carries the number, so a workgroup knows from its arguments
+// and its ticket whether it is in a group: no memory of the caller's is used in between, and
+// launches that overlap, on any streams and from any threads, never share a state.  (Bases
+// follow one another, so launches that overlap meet only where their rows together outnumber
+// the states, or in replays of graphs.)  The last member to leave a row gives its state back.
+// The replays of a graph's node share its number.  Should two instances of one captured call
+// run at once, a member of either may take a ticket (their arguments are the same), each
+// ticket is taken once, and a row's first workgroup that finds its own gone does the row.
+//
+// The exchanges of a launch are numbered on from those of the state's earlier launches, so
+// its words need no clearing: no word in a state carries a number that is still to come.
 //
 // A group whose exchange times out (members preempted for 20 ms, say) does not fail the row
 // here: its first workgroup does the row over, alone.  Measured: 64 rows of V = 128,257 bf16
 // with six candidates 129.7 us with one workgroup a row, 71.6 us with four (the claim's
 // launch included); one CU's vector ALU sets the time of a pass over such a row.
 constexpr int32_t kPoolGroups = 128;
-constexpr int32_t kClaimNone = 63, kClaimBase = 64;
 __device__ __align__(256) char g_pool[kPoolGroups * kGroupStride];
-__device__ uint32_t g_pool_used[kPoolGroups / 32];
+__device__ unsigned long long g_pool_owner[kPoolGroups];
+__device__ unsigned long long g_pool_tickets[kPoolGroups][kMaxGroup];
+// exchanges of one row, at most: two passes 1, the maxima between them, a rejection pass a
+// candidate (a round number beyond; even, as the exchange buffers alternate)
+constexpr uint32_t kPoolEpochs = 128;
+static_assert(kMaxCand + 3 <= (int)kPoolEpochs, "a row's exchanges must fit its share of the numbers");
 
-__device__ __forceinline__ int32_t* claim_of(const KParams& P, int64_t row) {
-    return (P.flat ? P.out_len : P.node_status) + row;
+struct PoolArgs {
+    unsigned long long id;   // the launch's number (not 0)
+    int32_t base;            // the first row's state
+};
+__device__ __forceinline__ char* pool_state(int32_t at) { return g_pool + (int64_t)at * kGroupStride; }
+__device__ __forceinline__ uint32_t pool_load(const char* word) {
+    return __hip_atomic_load(reinterpret_cast<const uint32_t*>(word), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void pool_store(char* word, uint32_t v) {
+    __hip_atomic_store(reinterpret_cast<uint32_t*>(word), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void __launch_bounds__(kResetBlock) rs_pool_claim(const KParams P) {
-    __shared__ int32_t s_slot;
-    const int32_t g = blockIdx.x;
-    int32_t b, n;
-    const int64_t row = group_row(P, g, b, n);
-    if (threadIdx.x == 0) {
-        // row g tries state g first, so the rows of a launch meet only where other launches
-        // hold states
-        int32_t slot = -1;
-        for (int32_t k = 0; k < kPoolGroups && slot < 0; ++k) {
-            const int32_t at = (g + k) % kPoolGroups;
-            const uint32_t bit = 1u << (at & 31);
-            if (!(atomicOr(&g_pool_used[at >> 5], bit) & bit)) slot = at;
-        }
-        *claim_of(P, row) = slot < 0 ? kClaimNone : kClaimBase + slot;
-        s_slot = slot;
+__global__ void __launch_bounds__(kPoolGroups) rs_pool_claim(const PoolArgs pa, int32_t nrows, int32_t S) {
+    const int32_t g = threadIdx.x, at = (pa.base + g) % kPoolGroups;
+    const bool mine = g < nrows && atomicCAS(&g_pool_owner[at], 0ull, pa.id) == 0ull;
+    if (__syncthreads_and(g >= nrows || mine)) {
+        for (int32_t m = 0; mine && m < S; ++m) g_pool_tickets[at][m] = pa.id;
+    } else if (mine) {
+        atomicExch(&g_pool_owner[at], 0ull);
     }
-    __syncthreads();
-    if (s_slot < 0) return;
-    unsigned long long* words = reinterpret_cast<unsigned long long*>(g_pool + s_slot * kGroupStride);
-    for (int64_t k = threadIdx.x; k < kGroupWordsEnd / (int64_t)sizeof(unsigned long long); k += kResetBlock)
-        words[k] = 0ull;
+}
+
+// A state whose members have all left goes back: everything but its owner first, all of it
+// in atomic words that have landed before the owner's goes.
+__device__ __forceinline__ void pool_give_back(int32_t at) {
+    char* state = pool_state(at);
+    uint32_t epoch = pool_load(state + kGroupEpoch) + kPoolEpochs;
+    if (epoch > ~0u - kPoolEpochs) {
+        // the numbers start again (after 2^25 launches): no word may keep an old one
+        for (int64_t k = kGroupXw; k < kGroupWordsEnd; k += (int64_t)sizeof(uint32_t)) pool_store(state + k, 0u);
+        epoch = 0u;
+    }
+    pool_store(state + kGroupEpoch, epoch);
+    pool_store(state + kGroupArrive, 0u);
+    pool_store(state + kGroupState, kFormOpen);
+    pool_store(state + kGroupLeave, 0u);
+    __threadfence();
+    atomicExch(&g_pool_owner[at], 0ull);
 }
 
 template <typename In, int VEC, int UNR, int MODE>
 __global__ void __launch_bounds__(kPathBlock) __attribute__((amdgpu_waves_per_eu(2)))
-rs_poolgroup_kernel(const KParams P, const GroupArgs ga) {
+rs_poolgroup_kernel(const KParams P, const GroupArgs ga, const PoolArgs pa) {
     __shared__ Smem sm;
     const int32_t S = ga.S;
     int32_t g, member, b, n;
     if (!group_of(ga, g, member)) return;
     const int64_t row = group_row(P, g, b, n);
-    const int32_t slot = __builtin_amdgcn_readfirstlane(*claim_of(P, row)) - kClaimBase;
-    // no state: the first workgroup does the row (the others may find its outcome here)
-    if (slot < 0 && member != 0) return;
-    char* base = g_pool + max(slot, 0) * kGroupStride;
+    const int32_t at = (pa.base + g) % kPoolGroups;
+    char* base = pool_state(at);
     RowGroup grp{S, member, reinterpret_cast<unsigned long long*>(base + kGroupXw),
                  reinterpret_cast<unsigned long long*>(base + kGroupXm), 0u, ga.wait};
-    bool lead = member == 0;
-    const int form = slot < 0 ? 2 : form_group(sm, grp, base, ga.form_wait);
-    if (form == 2) {
+    const int form = form_group(sm, grp, base, ga.form_wait, &g_pool_tickets[at][member], pa.id);
+    if (form == 3 && member != 0) return;   // no group: the first workgroup does the row
+    const bool lead = form == 1 ? member == 0 : form != 0;
+    if (form > 1) {
         grp.S = 1;
         grp.w = 0;
-        lead = true;
+    } else {
+        grp.epoch = __builtin_amdgcn_readfirstlane(pool_load(base + kGroupEpoch));
     }
     if (form != 0) {
         for (;;) {
@@ -1897,25 +1924,12 @@ rs_poolgroup_kernel(const KParams P, const GroupArgs ga) {
         }
     }
     if (threadIdx.x != 0) return;
-    if (slot < 0) {
-        write_outcome(P, row, sm.res_child, sm.res_tok, sm.res_status);
-        return;
-    }
-    // Leaving.  Every word that a member published has been read by every member (or the
-    // fence above has passed), so nothing of this launch is still on its way to the state
-    // when the last member gives it back.
-    unsigned long long* out = reinterpret_cast<unsigned long long*>(base + kGroupOutcome);
-    if (lead && form != 0) {
-        put_tagged(out, 1u, (uint32_t)sm.res_child);
-        put_tagged(out + 1, 1u, (uint32_t)sm.res_tok);
-        put_tagged(out + 2, 1u, (uint32_t)sm.res_status);
-    }
-    if (atomicAdd(reinterpret_cast<uint32_t*>(base + kGroupLeave), 1u) + 1u != (uint32_t)S) return;
-    const unsigned long long* const w[3] = {out, out + 1, out + 2};
-    uint32_t v[3] = {~0u, ~0u, (uint32_t)RS_SEQ_GROUP_TIMEOUT};
-    get_tagged_all<3>(w, 1u, v, (uint64_t)wall_clock64(), kGroupWaitTicks);
-    write_outcome(P, row, (int32_t)v[0], (int32_t)v[1], (int32_t)v[2]);
-    atomicAnd(&g_pool_used[slot >> 5], ~(1u << (slot & 31)));
+    if (lead) write_outcome(P, row, sm.res_child, sm.res_tok, sm.res_status);
+    // Leaving.  Every word that a member published has been read by every member, itself
+    // included, or the fence above has passed: nothing of this launch is still on its way to
+    // the state when the last member gives it back.
+    if (form != 3 && atomicAdd(reinterpret_cast<uint32_t*>(base + kGroupLeave), 1u) + 1u == (uint32_t)S)
+        pool_give_back(at);
 }
 
 // ----------------------------------------------------------- walk kernel ----
@@ -2211,6 +2225,11 @@ GroupArgs group_args(int32_t S, char* ws, int64_t groups) {
     return GroupArgs{S, ws, g_group_wait.load(std::memory_order_relaxed),
                      g_form_wait.load(std::memory_order_relaxed), (int32_t)groups, xcd ? 1 : 0};
 }
+// The next launch's number and states in the pool.
+PoolArgs pool_args(int32_t nrows) {
+    static std::atomic<unsigned long long> launches{0}, rows{0};
+    return PoolArgs{launches.fetch_add(1) + 1, (int32_t)(rows.fetch_add((unsigned long long)nrows) % kPoolGroups)};
+}
 unsigned group_grid(const GroupArgs& ga) {
     const int64_t groups = ga.xcd ? (ga.groups + kXcds - 1) / kXcds * kXcds : (int64_t)ga.groups;
     return (unsigned)(groups * ga.S);
@@ -2223,12 +2242,13 @@ hipError_t launch_row_kernel(KParams P, int64_t nrows, bool pool, hipStream_t s)
         // few long rows: row groups in the library's pool
         const int32_t S = pool && nrows <= kPoolGroups && !P.residual_out ? auto_row_group<In>(P, nrows, kMaxGroup) : 1;
         if (S > 1) {
-            hipLaunchKernelGGL(rs_pool_claim, dim3((unsigned)nrows), dim3(kResetBlock), 0, s, P);
+            const PoolArgs pa = pool_args((int32_t)nrows);
+            hipLaunchKernelGGL(rs_pool_claim, dim3(1), dim3(kPoolGroups), 0, s, pa, (int32_t)nrows, S);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
             const GroupArgs ga = group_args(S, nullptr, nrows);
             hipLaunchKernelGGL((rs_poolgroup_kernel<In, VEC, UNR, MODE>), dim3(group_grid(ga)), dim3(kPathBlock), 0, s,
-                               P, ga);
+                               P, ga, pa);
             return hipGetLastError();
         }
     }
@@ -2759,6 +2779,14 @@ rs_status resispec_debug_set_group_waits(uint64_t barrier_ticks, uint64_t format
     g_group_wait.store(barrier_ticks == UINT64_MAX ? kGroupWaitTicks : barrier_ticks, std::memory_order_relaxed);
     g_form_wait.store(formation_ticks == UINT64_MAX ? kFormWaitTicks : formation_ticks, std::memory_order_relaxed);
     return RS_OK;
+}
+
+int32_t resispec_debug_pool_held(void) {
+    unsigned long long owner[kPoolGroups];
+    if (hipDeviceSynchronize() != hipSuccess ||
+        hipMemcpyFromSymbol(owner, HIP_SYMBOL(g_pool_owner), sizeof(owner)) != hipSuccess)
+        return -1;
+    return (int32_t)(kPoolGroups - std::count(owner, owner + kPoolGroups, 0ull));
 }
 
 size_t resispec_path_workspace_bytes(int32_t B, int32_t V) {

@@ -28,7 +28,7 @@ EXPORTS = ("resispec_verify", "resispec_verify_tree", "resispec_verify_tree_noal
            "resispec_deferred_workspace_bytes",
            "resispec_verify_tree_path",
            "resispec_verify_tree_path_group", "resispec_path_workspace_bytes",
-           "resispec_path_group_size", "resispec_debug_set_group_waits",
+           "resispec_path_group_size", "resispec_debug_set_group_waits", "resispec_debug_pool_held",
            "resispec_verify_tree_group", "resispec_tree_group_workspace_bytes",
            "resispec_tree_group_size",
            "resispec_draft_candidates",
@@ -74,6 +74,8 @@ def _load():
     lib.resispec_path_group_size.restype = i32
     lib.resispec_debug_set_group_waits.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
     lib.resispec_debug_set_group_waits.restype = i32
+    lib.resispec_debug_pool_held.argtypes = []
+    lib.resispec_debug_pool_held.restype = i32
     lib.resispec_verify_tree_group.argtypes = [P, P, P, P, P, P, i32, i32, i32, i32, prm, P, P, P,
                                                i32, P, sz, P]
     lib.resispec_verify_tree_group.restype = i32
@@ -423,6 +425,15 @@ def resispec_debug_set_group_waits(barrier=None, formation=None) -> None:
     _check(lib.resispec_debug_set_group_waits(
         ctypes.c_uint64(none if barrier is None else int(barrier)),
         ctypes.c_uint64(none if formation is None else int(formation))))
+
+
+def resispec_debug_pool_held() -> int:
+    """Testing hook: group states of the library's pool in use on the current device, after a
+    synchronisation; 0 unless something went wrong."""
+    n = lib.resispec_debug_pool_held()
+    if n < 0:
+        raise RuntimeError("the pool of group states cannot be read")
+    return n
 
 
 def resispec_verify_tree_path_group(target_logits, draft_logits, node_token, parent, u_accept,
