@@ -111,8 +111,9 @@ typedef struct {
  * whose exchange states come from a pool of 128 that the library keeps on each GPU; calls may
  * overlap on any streams and threads, and replay from graphs.  The results are the same bit
  * for bit, outputs are written with the outcomes and not before, and RS_SEQ_GROUP_TIMEOUT is
- * not reported: a row whose workgroups lose touch (20 ms), or a call that meets another's
- * states, is done by one workgroup a row.
+ * not reported: a row whose workgroups lose touch (20 ms), and every row of a call that
+ * meets others of its kind and would not have a CU for each workgroup, is done by one
+ * workgroup.
  */
 rs_status resispec_verify(const void* target_logits, const void* draft_logits,
                           const int32_t* cand_ids, const float* u_accept,
@@ -339,9 +340,9 @@ int32_t resispec_tree_group_size(int32_t B, int32_t N, int32_t V, const rs_param
  * Not for concurrent use with launches on other threads.  Always RS_OK. */
 rs_status resispec_debug_set_group_waits(uint64_t barrier_ticks, uint64_t formation_ticks);
 
-/* Testing hook: how many of the pool's group states (resispec_verify, above) are in use on
- * the current device once it has been synchronised, which the call does; 0 unless something
- * went wrong, -1 for a HIP error. */
+/* Testing hook: how many of the pool's group states (resispec_verify, above) are in use, and
+ * workgroups counted, on the current device once it has been synchronised, which the call
+ * does; 0 unless something went wrong, -1 for a HIP error. */
 int32_t resispec_debug_pool_held(void);
 
 /* Workspace bytes resispec_verify_tree_path_group needs for B sequences of V-element rows

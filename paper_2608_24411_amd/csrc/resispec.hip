@@ -257,7 +257,7 @@ __device__ __forceinline__ int form_group(Smem& sm, const RowGroup& g, char* bas
             }
             __builtin_amdgcn_s_sleep(2);
         }
-        __threadfence();
+        if (res != 3) __threadfence();
         sm.group_ok = res;
     }
     __syncthreads();
@@ -1816,8 +1816,8 @@ rs_rowgroup_kernel(const KParams P, const GroupArgs ga) {
 // that the library keeps on each GPU (kPoolGroups states, about 1.2 MB).  Row g of a launch
 // uses state (base + g) % kPoolGroups, or none.  A launch before the groups' takes all of
 // the launch's states, by its number in the states' owner words (0: free), and lays out a ticket for
-// every member; or, where another launch has one of them, takes none, and the first
-// workgroup of every row does the row alone.  Numbers and bases are given out on the host,
+// every member; or, where another launch has one of them or the CUs are taken (below), takes
+// none, and the first workgroup of every row does the row alone.  Numbers and bases are given out on the host,
 // one to a call, and a ticket carries the number, so a workgroup knows from its arguments
 // and its ticket whether it is in a group: no memory of the caller's is used in between, and
 // launches that overlap, on any streams and from any threads, never share a state.  (Bases
@@ -1838,6 +1838,9 @@ constexpr int32_t kPoolGroups = 128;
 __device__ __align__(256) char g_pool[kPoolGroups * kGroupStride];
 __device__ unsigned long long g_pool_owner[kPoolGroups];
 __device__ unsigned long long g_pool_tickets[kPoolGroups][kMaxGroup];
+// workgroups of launches between their claim and their rows' ends: a group's members, one for
+// a row without a group
+__device__ uint32_t g_pool_wgs;
 // exchanges of one row, at most: two passes 1, the maxima between them, a rejection pass a
 // candidate (a round number beyond; even, as the exchange buffers alternate)
 constexpr uint32_t kPoolEpochs = 128;
@@ -1855,19 +1858,50 @@ __device__ __forceinline__ void pool_store(char* word, uint32_t v) {
     __hip_atomic_store(reinterpret_cast<uint32_t*>(word), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void __launch_bounds__(kPoolGroups) rs_pool_claim(const PoolArgs pa, int32_t nrows, int32_t S) {
+// Groups pay where the device is otherwise idle: S members take S times a CU for a row, and
+// finish it less than S times sooner.  So a launch takes its states only if its workgroups
+// and those of the launches under way have a CU each (most: the CUs).  us a call, V = 128,256
+// bf16, four candidates, calls on 1, 2, 3 and 4 streams at once:
+//              32 rows                  64 rows                  128 rows
+//   no groups  76   40   28   23        79   43   30   24        84   46   36   32
+//   always     43   30   29   27        51   53   47   48        73   67   64   62
+//   this rule  43   31   26   23        51   44   32   25        72   48   37   33
+__global__ void __launch_bounds__(kPoolGroups) rs_pool_claim(const PoolArgs pa, int32_t nrows, int32_t S,
+                                                             uint32_t most) {
     const int32_t g = threadIdx.x, at = (pa.base + g) % kPoolGroups;
+    const uint32_t n = (uint32_t)(nrows * S);
+    const bool room = g != 0 || atomicAdd(&g_pool_wgs, n) + n <= most;
     const bool mine = g < nrows && atomicCAS(&g_pool_owner[at], 0ull, pa.id) == 0ull;
-    if (__syncthreads_and(g >= nrows || mine)) {
+    if (__syncthreads_and(room && (g >= nrows || mine))) {
         for (int32_t m = 0; mine && m < S; ++m) g_pool_tickets[at][m] = pa.id;
-    } else if (mine) {
-        atomicExch(&g_pool_owner[at], 0ull);
+        return;
     }
+    if (mine) atomicExch(&g_pool_owner[at], 0ull);
+    if (g == 0) atomicSub(&g_pool_wgs, n - (uint32_t)nrows);
+}
+
+// Which group and member a workgroup is: the layout of group_of, but the first members of all
+// groups come first in the grid.  Where a launch has no groups they are the ones with work,
+// and in the order of group_of they wait for a CU behind workgroups that only leave (at 512
+// threads a member, 64 rows on four streams 59 us a call, with this 28 us).
+__device__ __forceinline__ bool pool_group_of(const GroupArgs& ga, int32_t& g, int32_t& w) {
+    const int32_t X = (int32_t)kXcds;
+    const int32_t leads = ga.xcd ? (ga.groups + X - 1) / X * X : ga.groups;
+    const int32_t i = (int32_t)blockIdx.x, h = i - leads, rest = ga.S - 1;
+    if (h < 0) {
+        g = i;
+        w = 0;
+    } else {
+        const int32_t k = ga.xcd ? h / X : h;
+        g = ga.xcd ? h % X + X * (k / rest) : k / rest;
+        w = 1 + k % rest;
+    }
+    return g < ga.groups;
 }
 
 // A state whose members have all left goes back: everything but its owner first, all of it
 // in atomic words that have landed before the owner's goes.
-__device__ __forceinline__ void pool_give_back(int32_t at) {
+__device__ __forceinline__ void pool_give_back(int32_t at, int32_t S) {
     char* state = pool_state(at);
     uint32_t epoch = pool_load(state + kGroupEpoch) + kPoolEpochs;
     if (epoch > ~0u - kPoolEpochs) {
@@ -1881,15 +1915,20 @@ __device__ __forceinline__ void pool_give_back(int32_t at) {
     pool_store(state + kGroupLeave, 0u);
     __threadfence();
     atomicExch(&g_pool_owner[at], 0ull);
+    atomicSub(&g_pool_wgs, (uint32_t)S);
 }
 
+// 768 threads a member, as a row takes where it has a CU to itself (kLoneBlock): where there
+// are no groups, that is what the launch is.  The code of a row alone stands apart from a
+// group's (one loop over both held 222 registers; at 512 threads a member 128 rows on two
+// streams took 53 us a call, with this 48).
 template <typename In, int VEC, int UNR, int MODE>
-__global__ void __launch_bounds__(kPathBlock) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(kLoneBlock) __attribute__((amdgpu_waves_per_eu(3)))
 rs_poolgroup_kernel(const KParams P, const GroupArgs ga, const PoolArgs pa) {
     __shared__ Smem sm;
     const int32_t S = ga.S;
     int32_t g, member, b, n;
-    if (!group_of(ga, g, member)) return;
+    if (!pool_group_of(ga, g, member)) return;
     const int64_t row = group_row(P, g, b, n);
     const int32_t at = (pa.base + g) % kPoolGroups;
     char* base = pool_state(at);
@@ -1898,38 +1937,37 @@ rs_poolgroup_kernel(const KParams P, const GroupArgs ga, const PoolArgs pa) {
     const int form = form_group(sm, grp, base, ga.form_wait, &g_pool_tickets[at][member], pa.id);
     if (form == 3 && member != 0) return;   // no group: the first workgroup does the row
     const bool lead = form == 1 ? member == 0 : form != 0;
-    if (form > 1) {
-        grp.S = 1;
-        grp.w = 0;
-    } else {
+    const auto keep = [&](int32_t child, int32_t tok, int32_t st) {
+        sm.res_child = child;
+        sm.res_tok = tok;
+        sm.res_status = st;
+    };
+    bool alone = form > 1;
+    if (form == 1) {
         grp.epoch = __builtin_amdgcn_readfirstlane(pool_load(base + kGroupEpoch));
-    }
-    if (form != 0) {
-        for (;;) {
-            verify_row<In, VEC, UNR, MODE, kPathBlock, true>(P, sm, row, b, n,
-                                                         [&](int32_t child, int32_t tok, int32_t st) {
-                sm.res_child = child;
-                sm.res_tok = tok;
-                sm.res_status = st;
-            }, grp);
-            __syncthreads();
-            const int32_t st = __builtin_amdgcn_readfirstlane(sm.res_status);
-            if (st != RS_SEQ_GROUP_TIMEOUT || grp.S == 1) break;
+        verify_row<In, VEC, UNR, MODE, kLoneBlock, true>(P, sm, row, b, n, keep, grp);
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(sm.res_status) == RS_SEQ_GROUP_TIMEOUT) {
             // words of this member that no other has read yet land before it leaves
             __threadfence();
             __syncthreads();
-            if (!lead) break;
-            grp.S = 1;
-            grp.w = 0;
+            alone = lead;
         }
+    }
+    if (alone) {
+        RowGroup solo{1, 0, nullptr, nullptr, 0u, ga.wait};
+        verify_row<In, VEC, UNR, MODE, kLoneBlock, false>(P, sm, row, b, n, keep, solo);
+        __syncthreads();
     }
     if (threadIdx.x != 0) return;
     if (lead) write_outcome(P, row, sm.res_child, sm.res_tok, sm.res_status);
     // Leaving.  Every word that a member published has been read by every member, itself
     // included, or the fence above has passed: nothing of this launch is still on its way to
     // the state when the last member gives it back.
-    if (form != 3 && atomicAdd(reinterpret_cast<uint32_t*>(base + kGroupLeave), 1u) + 1u == (uint32_t)S)
-        pool_give_back(at);
+    if (form == 3)
+        atomicSub(&g_pool_wgs, 1u);
+    else if (atomicAdd(reinterpret_cast<uint32_t*>(base + kGroupLeave), 1u) + 1u == (uint32_t)S)
+        pool_give_back(at, S);
 }
 
 // ----------------------------------------------------------- walk kernel ----
@@ -2243,11 +2281,12 @@ hipError_t launch_row_kernel(KParams P, int64_t nrows, bool pool, hipStream_t s)
         const int32_t S = pool && nrows <= kPoolGroups && !P.residual_out ? auto_row_group<In>(P, nrows, kMaxGroup) : 1;
         if (S > 1) {
             const PoolArgs pa = pool_args((int32_t)nrows);
-            hipLaunchKernelGGL(rs_pool_claim, dim3(1), dim3(kPoolGroups), 0, s, pa, (int32_t)nrows, S);
+            hipLaunchKernelGGL(rs_pool_claim, dim3(1), dim3(kPoolGroups), 0, s, pa, (int32_t)nrows, S,
+                               (uint32_t)cu_count());
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
             const GroupArgs ga = group_args(S, nullptr, nrows);
-            hipLaunchKernelGGL((rs_poolgroup_kernel<In, VEC, UNR, MODE>), dim3(group_grid(ga)), dim3(kPathBlock), 0, s,
+            hipLaunchKernelGGL((rs_poolgroup_kernel<In, VEC, UNR, MODE>), dim3(group_grid(ga)), dim3(kLoneBlock), 0, s,
                                P, ga, pa);
             return hipGetLastError();
         }
@@ -2783,10 +2822,12 @@ rs_status resispec_debug_set_group_waits(uint64_t barrier_ticks, uint64_t format
 
 int32_t resispec_debug_pool_held(void) {
     unsigned long long owner[kPoolGroups];
+    uint32_t wgs = 0;
     if (hipDeviceSynchronize() != hipSuccess ||
-        hipMemcpyFromSymbol(owner, HIP_SYMBOL(g_pool_owner), sizeof(owner)) != hipSuccess)
+        hipMemcpyFromSymbol(owner, HIP_SYMBOL(g_pool_owner), sizeof(owner)) != hipSuccess ||
+        hipMemcpyFromSymbol(&wgs, HIP_SYMBOL(g_pool_wgs), sizeof(wgs)) != hipSuccess)
         return -1;
-    return (int32_t)(kPoolGroups - std::count(owner, owner + kPoolGroups, 0ull));
+    return (int32_t)((kPoolGroups - std::count(owner, owner + kPoolGroups, 0ull) + wgs) & 0x7fffffffu);
 }
 
 size_t resispec_path_workspace_bytes(int32_t B, int32_t V) {

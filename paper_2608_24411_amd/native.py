@@ -428,8 +428,8 @@ def resispec_debug_set_group_waits(barrier=None, formation=None) -> None:
 
 
 def resispec_debug_pool_held() -> int:
-    """Testing hook: group states of the library's pool in use on the current device, after a
-    synchronisation; 0 unless something went wrong."""
+    """Testing hook: group states of the library's pool in use, and workgroups counted, on the
+    current device, after a synchronisation; 0 unless something went wrong."""
     n = lib.resispec_debug_pool_held()
     if n < 0:
         raise RuntimeError("the pool of group states cannot be read")

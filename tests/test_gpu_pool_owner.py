@@ -128,3 +128,22 @@ def test_many_launches(gpu_lib, one):
             equal(out, [x[50:80] for x in ref])
         equal(got, [x[i % 100:i % 100 + B] for x in ref])
     assert gpu_lib.resispec_debug_pool_held() == 0
+
+
+def test_launches_that_meet(gpu_lib, one):
+    """Launches of 64 and 128 rows on two and four streams: some take groups and some do not,
+    every row is right, and the count of workgroups under way ends at 0."""
+    w, ref = one
+    for B, ns in ((64, 2), (128, 2), (128, 4), (20, 4)):
+        print("pool, launches that meet", B, ns, flush=True)
+        streams = [torch.cuda.Stream() for _ in range(ns)]
+        torch.cuda.synchronize()
+        outs = []
+        for i in range(12):
+            for s in streams:
+                with torch.cuda.stream(s):
+                    outs.append((i, flat(gpu_lib, w, B, i)))
+        torch.cuda.synchronize()
+        for i, out in outs:
+            equal(out, [x[i:i + B] for x in ref])
+        assert gpu_lib.resispec_debug_pool_held() == 0
