@@ -345,6 +345,10 @@ rs_status resispec_debug_set_group_waits(uint64_t barrier_ticks, uint64_t format
  * does; 0 unless something went wrong, -1 for a HIP error. */
 int32_t resispec_debug_pool_held(void);
 
+/* Testing hook: the next n launches of the pool's groups in this process count as failed
+ * (the calls return RS_ERR_HIP and their states go back); 0 ends that.  Always RS_OK. */
+rs_status resispec_debug_fail_pool_launches(int32_t n);
+
 /* Workspace bytes resispec_verify_tree_path_group needs for B sequences of V-element rows
  * (0 if B <= 0, V <= 0 or V > RS_MAX_VOCAB): one row-group state per sequence, then two
  * fp32 rows per sequence (V rounded up to a multiple of 1024 each), in which the ResiSpec

@@ -1880,6 +1880,14 @@ __global__ void __launch_bounds__(kPoolGroups) rs_pool_claim(const PoolArgs pa, 
     if (g == 0) atomicSub(&g_pool_wgs, n - (uint32_t)nrows);
 }
 
+// Undoes a claim whose rows' launch failed.
+__global__ void __launch_bounds__(kPoolGroups) rs_pool_release(const PoolArgs pa, int32_t nrows, int32_t S) {
+    const int32_t g = threadIdx.x, at = (pa.base + g) % kPoolGroups;
+    if (g >= nrows) return;
+    const bool mine = atomicCAS(&g_pool_owner[at], pa.id, 0ull) == pa.id;
+    atomicSub(&g_pool_wgs, mine ? (uint32_t)S : 1u);
+}
+
 // Which group and member a workgroup is: the layout of group_of, but the first members of all
 // groups come first in the grid.  Where a launch has no groups they are the ones with work,
 // and in the order of group_of they wait for a CU behind workgroups that only leave (at 512
@@ -2263,6 +2271,12 @@ GroupArgs group_args(int32_t S, char* ws, int64_t groups) {
     return GroupArgs{S, ws, g_group_wait.load(std::memory_order_relaxed),
                      g_form_wait.load(std::memory_order_relaxed), (int32_t)groups, xcd ? 1 : 0};
 }
+// Whether this launch of the pool's groups is to count as failed (a testing hook).
+std::atomic<int32_t> g_fail_pool{0};
+bool fail_pool_launch() {
+    return g_fail_pool.load(std::memory_order_relaxed) > 0 && g_fail_pool.fetch_sub(1) > 0;
+}
+
 // The next launch's number and states in the pool.
 PoolArgs pool_args(int32_t nrows) {
     static std::atomic<unsigned long long> launches{0}, rows{0};
@@ -2286,9 +2300,17 @@ hipError_t launch_row_kernel(KParams P, int64_t nrows, bool pool, hipStream_t s)
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
             const GroupArgs ga = group_args(S, nullptr, nrows);
-            hipLaunchKernelGGL((rs_poolgroup_kernel<In, VEC, UNR, MODE>), dim3(group_grid(ga)), dim3(kLoneBlock), 0, s,
-                               P, ga, pa);
-            return hipGetLastError();
+            hipError_t launched = hipErrorLaunchFailure;
+            if (!fail_pool_launch()) {
+                hipLaunchKernelGGL((rs_poolgroup_kernel<In, VEC, UNR, MODE>), dim3(group_grid(ga)), dim3(kLoneBlock),
+                                   0, s, P, ga, pa);
+                launched = hipGetLastError();
+            }
+            if (launched != hipSuccess) {
+                hipLaunchKernelGGL(rs_pool_release, dim3(1), dim3(kPoolGroups), 0, s, pa, (int32_t)nrows, S);
+                (void)hipGetLastError();
+            }
+            return launched;
         }
     }
     if (VEC > 1 && nrows <= cu_count())
@@ -2817,6 +2839,11 @@ rs_status resispec_verify_tree_path_group(const void* target_logits, const void*
 rs_status resispec_debug_set_group_waits(uint64_t barrier_ticks, uint64_t formation_ticks) {
     g_group_wait.store(barrier_ticks == UINT64_MAX ? kGroupWaitTicks : barrier_ticks, std::memory_order_relaxed);
     g_form_wait.store(formation_ticks == UINT64_MAX ? kFormWaitTicks : formation_ticks, std::memory_order_relaxed);
+    return RS_OK;
+}
+
+rs_status resispec_debug_fail_pool_launches(int32_t n) {
+    g_fail_pool.store(n);
     return RS_OK;
 }
 

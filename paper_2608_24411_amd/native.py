@@ -29,6 +29,7 @@ EXPORTS = ("resispec_verify", "resispec_verify_tree", "resispec_verify_tree_noal
            "resispec_verify_tree_path",
            "resispec_verify_tree_path_group", "resispec_path_workspace_bytes",
            "resispec_path_group_size", "resispec_debug_set_group_waits", "resispec_debug_pool_held",
+           "resispec_debug_fail_pool_launches",
            "resispec_verify_tree_group", "resispec_tree_group_workspace_bytes",
            "resispec_tree_group_size",
            "resispec_draft_candidates",
@@ -76,6 +77,8 @@ def _load():
     lib.resispec_debug_set_group_waits.restype = i32
     lib.resispec_debug_pool_held.argtypes = []
     lib.resispec_debug_pool_held.restype = i32
+    lib.resispec_debug_fail_pool_launches.argtypes = [i32]
+    lib.resispec_debug_fail_pool_launches.restype = i32
     lib.resispec_verify_tree_group.argtypes = [P, P, P, P, P, P, i32, i32, i32, i32, prm, P, P, P,
                                                i32, P, sz, P]
     lib.resispec_verify_tree_group.restype = i32
@@ -434,6 +437,11 @@ def resispec_debug_pool_held() -> int:
     if n < 0:
         raise RuntimeError("the pool of group states cannot be read")
     return n
+
+
+def resispec_debug_fail_pool_launches(n: int) -> None:
+    """Testing hook: the next n launches of the pool's groups count as failed."""
+    _check(lib.resispec_debug_fail_pool_launches(int(n)))
 
 
 def resispec_verify_tree_path_group(target_logits, draft_logits, node_token, parent, u_accept,

@@ -147,3 +147,18 @@ def test_launches_that_meet(gpu_lib, one):
         for i, out in outs:
             equal(out, [x[i:i + B] for x in ref])
         assert gpu_lib.resispec_debug_pool_held() == 0
+
+
+def test_a_launch_that_fails_keeps_no_state(gpu_lib, one):
+    w, ref = one
+    print("pool, failed launches", flush=True)
+    gpu_lib.resispec_debug_fail_pool_launches(3)
+    try:
+        for B in (128, 1, 60):
+            with pytest.raises(RuntimeError):
+                flat(gpu_lib, w, B)
+        assert gpu_lib.resispec_debug_pool_held() == 0
+        equal(flat(gpu_lib, w, 64, 9), [x[9:73] for x in ref])     # the fourth does not fail
+    finally:
+        gpu_lib.resispec_debug_fail_pool_launches(0)
+    assert gpu_lib.resispec_debug_pool_held() == 0
