@@ -410,8 +410,9 @@ rs_status resispec_walk(const int32_t* node_token, int32_t B, int32_t N, int32_t
 
 /*
  * Every node's own outcome as resispec_verify_nodes left it in `workspace` (the same
- * B and N, earlier on the same stream), copied into caller arrays (device-to-device,
- * stream-ordered, asynchronous): the outcome of Algorithm 1 at each node, as the debug
+ * B and N, earlier on the same stream), copied into caller arrays (stream-ordered,
+ * asynchronous; on the current device, the usual case, by one kernel, elsewhere by the
+ * runtime's copies): the outcome of Algorithm 1 at each node, as the debug
  * entry below reports it.  The workspace of resispec_decide_nodes (and resispec_walk_draw)
  * is read the same way; there, nodes whose draw was deferred and not made report
  * RS_SEQ_DEFERRED.

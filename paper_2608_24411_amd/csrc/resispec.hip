@@ -47,6 +47,7 @@
 // step that precedes verification is in draft.hip; shared helpers are in common.h.
 
 #include <algorithm>
+#include <initializer_list>
 #include <atomic>
 #include <mutex>
 
@@ -2093,6 +2094,7 @@ __global__ void __launch_bounds__(kWalkBlock) rs_walk_kernel(const int32_t* __re
 // The three outcome arrays of a workspace, copied in one launch (one element a thread: they
 // are a few hundred KB at most, so a launch is what a copy costs; with three copies the
 // outcomes of 32 trees of 60 nodes and their verification took 284.4 us, with this 280.8 us).
+// Destinations that a kernel may not reach take the runtime's copies.
 constexpr int kCopyBlock = 256;
 __global__ void __launch_bounds__(kCopyBlock) rs_outcomes_kernel(const int32_t* __restrict__ src, int64_t stride,
                                                                  int64_t rows, int32_t* __restrict__ child,
@@ -2611,6 +2613,22 @@ namespace {
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[64];   // per device, null until looked up
 
+// Whether a kernel launched on the stream is sure to reach 32-bit words at these addresses:
+// memory of the current device, whose stream it is.  (A copy by the runtime reaches more:
+// host memory, another GPU's, and streams of other devices.)
+bool kernel_reaches(hipStream_t s, std::initializer_list<const void*> words) {
+    int dev = 0;
+    hipDevice_t of = 0;
+    bool ok = hipGetDevice(&dev) == hipSuccess && hipStreamGetDevice(s, &of) == hipSuccess && of == dev;
+    for (const void* p : words) {
+        hipPointerAttribute_t at{};
+        ok = ok && reinterpret_cast<uintptr_t>(p) % sizeof(int32_t) == 0 &&
+             hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice && at.device == dev;
+    }
+    if (!ok) (void)hipGetLastError();   // an unknown address is an answer here
+    return ok;
+}
+
 // The current device's address of `scratch` (null if the lookup fails).
 void* scratch_ptr() {
     int dev = 0;
@@ -2923,6 +2941,14 @@ rs_status resispec_node_outcomes(const void* workspace, size_t workspace_bytes, 
         return RS_ERR_WORKSPACE;
     const int64_t rows = (int64_t)B * N;
     void* ws = const_cast<void*>(workspace);
+    int32_t* const dst[3] = {node_child, node_token_out, node_status};
+    if (!kernel_reaches((hipStream_t)stream, {workspace, dst[0], dst[1], dst[2]})) {
+        for (int k = 0; k < 3; ++k)
+            if (hipMemcpyAsync(dst[k], ws_array(ws, rows, k), (size_t)rows * sizeof(int32_t),
+                               hipMemcpyDefault, (hipStream_t)stream) != hipSuccess)
+                return RS_ERR_HIP;
+        return RS_OK;
+    }
     const int64_t blocks = (rows + kCopyBlock - 1) / kCopyBlock;
     hipLaunchKernelGGL(rs_outcomes_kernel, dim3((unsigned)blocks), dim3(kCopyBlock), 0, (hipStream_t)stream,
                        ws_array(ws, rows, 0), ws_array(ws, rows, 1) - ws_array(ws, rows, 0), rows, node_child,
