@@ -27,9 +27,10 @@
  *     reported per row / per sequence in out_status (rs_seq_status); the outputs
  *     of such a row/sequence are -1.
  *   - Logits rows are contiguous over the vocabulary.  fp32 or bf16 (raw bf16,
- *     widened exactly to fp32 in the kernel).  Rows whose byte length is a
- *     multiple of 16 and whose base pointer is 16-byte aligned take the
- *     vectorised path; any other V or alignment is handled element by element.
+ *     widened exactly to fp32 in the kernel).  Rows take 16-byte loads, whatever V
+ *     and the base pointer's alignment (a byte length that is a multiple of 16 on a
+ *     16-byte aligned base is somewhat faster); rows shorter than 16 bytes, and base
+ *     pointers not aligned to their elements, are handled element by element.
  *   - Uniforms are fp32 in [0, 1).  The accept test is strict: u < ratio.
  *   - Thread safety: calls are re-entrant.  What the library keeps on each GPU between
  *     calls, the pool of resispec_verify below and the scratch of
@@ -222,9 +223,9 @@ size_t resispec_deferred_workspace_bytes(int32_t B, int32_t N);
  * per-node outcomes go to a static device array of the library (one per GPU, held until
  * the process ends) sized for RS_NOALLOC_MAX_ROWS node rows (768 KiB).  The call
  * allocates nothing and nothing needs clearing: every call writes all B * N outcomes
- * before its walk reads them.  All calls on one GPU share that array, so calls that
- * overlap on one GPU (on different streams, or from different threads) race; calls
- * ordered on one stream do not.
+ * before its walk reads them.  All calls on one GPU share that array, so the outcomes of
+ * calls that overlap on one GPU (on different streams, or from different threads) race
+ * (theirs alone: other calls are not affected); calls ordered on one stream do not.
  * RS_ERR_UNSUPPORTED when B * N > RS_NOALLOC_MAX_ROWS; RS_ERR_HIP if the array's device
  * address cannot be found; otherwise the errors of resispec_verify_tree.
  */
@@ -272,7 +273,9 @@ rs_status resispec_verify_tree_path(const void* target_logits, const void* draft
  *                     workspace is NULL), 1 = one workgroup per sequence,
  *                     2..16 = that many (RS_ERR_UNSUPPORTED if B * group_size workgroups
  *                     cannot be resident at once or if a row has fewer slots than
- *                     members)
+ *                     members; rows that are not 16-byte aligned may be given as many
+ *                     members as they have runs of 256 elements, and run with as many
+ *                     as they have slots)
  *   workspace       : device buffer of at least resispec_path_workspace_bytes(B, V) bytes,
  *                     16-byte aligned, caller-owned; its counters and exchange words are
  *                     zeroed by the call itself (on `stream`) before the verification
@@ -306,7 +309,10 @@ rs_status resispec_verify_tree_path_group(const void* target_logits, const void*
  *                when that is under 2),
  *                1 = the ordinary kernel,
  *                2..16 = that many (RS_ERR_UNSUPPORTED if B * N * group_size workgroups
- *                cannot be resident at once or a row has fewer slots than members)
+ *                cannot be resident at once or a row has fewer slots than members; rows
+ *                that are not 16-byte aligned may be given up to two workgroups a CU, and
+ *                as many members as they have runs of 256 elements, and run with as many
+ *                as there is room and slots for)
  *   workspace  : device buffer of at least resispec_tree_group_workspace_bytes(B, N)
  *                bytes, 16-byte aligned, caller-owned (node outcomes, then one group
  *                state per row; its counters are zeroed by the call itself on `stream`).

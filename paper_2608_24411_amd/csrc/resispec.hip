@@ -2133,7 +2133,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
 // latencies (walk, description, draw): 1024 serving trees' step 763 -> 737 us.  Such rows
 // have one candidate or none, so the code of later rejections is left out, which is what
 // fits the pairs' 128 registers (the 128 trees of the benchmarked step also gained, 333 ->
-// 329 us).
+// 327 us).
 constexpr int kFinishBlock = 768;
 
 template <typename In, int VEC, int UNR, int MODE, int BLK>
