@@ -6,13 +6,12 @@ import subprocess
 
 import pytest
 
-from paper_2608_24411_amd import build, native
-
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 @pytest.fixture(scope="module")
 def program(tmp_path_factory):
+    from paper_2608_24411_amd import build
     env = {k: v for k, v in os.environ.items() if k != "LD_PRELOAD"}     # (a sanitizer's runtime)
     exe = str(tmp_path_factory.mktemp("cache") / "bounds")
     subprocess.run([build.HIPCC, "--offload-host-only", "-x", "hip", "-std=c++17", "-O1", "-w", "-I",
@@ -24,6 +23,8 @@ def program(tmp_path_factory):
 def test_cache_bounds(program):
     """Every size up to 1,200, then sizes spread to the largest, the ends of chunks and the
     sizes whose last slot is partial among them."""
+    # (not at import: the library would come before torch, and with it another HIP runtime)
+    from paper_2608_24411_amd import native
     edges = [k * 1024 + d for k in (128, 129, 130, 148, 149, 191, 257, 385, 1000, 4095) for d in (-1, 0, 1, 512, 513)]
     sizes = sorted(set(range(1, 1200)) | set(range(1201, 1 << 22, 4973)) | set(edges) |
                    {128256, 131073, 132000, 140000, 140001, 151643, 151669, 151936, 152064, 201088, 1 << 22})
