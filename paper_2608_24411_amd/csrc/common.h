@@ -393,6 +393,7 @@ struct Smem {
     // the candidates, whose masses are added in fp64, so the draft mass left after any
     // removals is a sum of what remains rather than a difference)
     uint32_t cand_slots[kMaxSlots / 32];
+    double Sd_nc;                   // draft mass outside the candidates (without replacement)
     // per-lane partials of every slot of the running pass ([lane][slot], padded so a
     // wave's 64 stores hit 64 distinct banks), reduced after the pass in a fixed order
     float partA[64][kMaxSlots + 1];

@@ -940,6 +940,7 @@ __device__ __forceinline__ void verify_row(const KParams& P, Smem& sm, const int
             if (lane == 0) {
                 sm.St = s0;
                 sm.Sd = sd;
+                sm.Sd_nc = s1;
                 sm.decision = ok ? -1 : -3;   // -3: sum again with exact maxima
                 sm.next_slot = kWaves;
             }
